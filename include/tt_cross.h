@@ -154,7 +154,7 @@ typedef struct tt_stats {
                                    distinct entries the greedy search evaluates; with rook
                                    pivoting the same measure (the search evaluates only the
                                    entries it looks at, counted in pivoted) */
-    int64_t pivoted;            /* residual entries scanned by argmax passes, all sweeps */
+    int64_t pivoted;            /* residual entries the argmax of each sweep covers, all sweeps */
     int64_t samples;            /* sample entries evaluated for rms and the first pivot */
     int32_t sweeps;             /* search sweeps run (the last one proposes nothing) */
     int32_t precision_used;     /* TT_PREC_FP64 or TT_PREC_FP32 */
@@ -173,8 +173,9 @@ typedef struct tt_stats {
                                    runs until neither step moves.  0 for greedy search */
     double sweep_kernel_s;      /* summed duration of those launches */
     double sweep_alg_bytes;     /* algorithmic residual traffic of the tile launches: 2w per
-                                   updated stored entry, w per scanned-only stored entry,
-                                   w per newly evaluated entry (w = 8 FP64, 4 FP32); rook
+                                   updated stored entry (entries that no new pivot changed are
+                                   not read again), w per newly evaluated entry (w = 8 FP64,
+                                   4 FP32); rook
                                    pivoting: 8 r_k per residual the search looked at (one
                                    factor vector streamed) */
     double new_entries;         /* superblock entries evaluated by the tile launches */

@@ -277,6 +277,13 @@ struct KSweep {
 
 // Tiles per unfolding of one sweep, split into new-entry tiles and stored
 // tiles, with the running offsets of both kinds over the unfoldings.
+//
+// An unfolding that committed nothing has no pivot to apply, and its masks
+// are as they were: its stored region is the superblock of the sweep before,
+// entry for entry, so the best candidate of that sweep (ProbState::prev) is
+// the region's and none of its tiles is visited (soff counts none).
+// Candidates lie densely per unfolding: its new tiles in order, then its
+// stored tiles.
 struct SweepShape {
     int RT[TT_MAX_D], CT[TT_MAX_D], RTs[TT_MAX_D], CTs[TT_MAX_D];
     int noff[TT_MAX_D + 1], soff[TT_MAX_D + 1];
@@ -287,6 +294,7 @@ struct ProbState {
     int r[2][TT_MAX_D + 1];       // committed ranks, double-buffered by sweep parity
     KSweep ks[TT_MAX_D];
     SweepShape sh;                // tile counts of the sweep ks describes
+    Cand prev[TT_MAX_D];          // best candidate of the superblock searched last
     int stop, capped, err, sweeps;
     unsigned long long pivoted;
     unsigned long long alg_bytes;   // algorithmic residual traffic of the tile launches

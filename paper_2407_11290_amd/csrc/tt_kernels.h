@@ -197,8 +197,8 @@ __device__ inline void block_best_t0(double &v, uint64_t &key, double &sv)
             if (better(s_v[i], s_k[i], v, key)) { v = s_v[i]; key = s_k[i]; sv = s_sv[i]; }
 }
 
-// Stored residuals, one wavefront per tile: apply the newest pivot (if any)
-// and search, in batches of B * (64 / TC) rows.  A 64-row chunk's first
+// Stored residuals, one wavefront per tile: apply the newest pivot and search
+// (an unfolding without a new pivot has no stored tiles to visit), in batches of B * (64 / TC) rows.  A 64-row chunk's first
 // batch goes out in one round of loads with the chunk's row masks and W
 // factors (and, for the first chunk, the column's mask and pivot-row entry),
 // from addresses that are always valid, and nothing loaded is used before
@@ -225,10 +225,9 @@ __device__ void stored_tile_wave(const KTile &K, const KSweep &ks, const TileGeo
     const gptr_t<const uint8_t> cpiv = as_global((const uint8_t *)K.cpiv);
     const int64_t ld = K.ld;
     const int col = g.col0 + (colok ? tcol : 0);
-    const bool apply = ks.apply != 0;
-    const int64_t urow = apply ? ks.arho : g.row0;   // any valid row when nothing is applied
-    const int wcol = apply ? ks.agam : col;
-    const V apiv = apply ? (V)ks.apiv : (V)1;
+    const int64_t urow = ks.arho;
+    const int wcol = ks.agam;
+    const V apiv = (V)ks.apiv;
     // chunk c0's row data: lane l holds row c0 + l's mask word and factor
     uint32_t rpl;
     V wl;
@@ -254,7 +253,7 @@ __device__ void stored_tile_wave(const KTile &K, const KSweep &ks, const TileGeo
     chunk_loads(0, nch);
     batch_loads(0, nch, 0);
     const bool live = colok && !cp;
-    const V u = apply ? ue / apiv : (V)0;
+    const V u = ue / apiv;
     // every lane runs the same iterations so that the shuffles see all lanes
     // (a value is used only for rows below nch, whose lanes loaded it)
     int c0 = 0, base = 0;
@@ -267,11 +266,8 @@ __device__ void stored_tile_wave(const KTile &K, const KSweep &ks, const TileGeo
             const int rp = (rw >> ((row & 3) * 8)) & 0xff;
             const V w = __shfl(wl, ii & 63, 64);
             if (ii < nch && live && !rp) {
-                V x = xv[b];
-                if (apply) {
-                    x = vfma<V>(-w, u, x);
-                    E[(int64_t)row * ld + col] = x;
-                }
+                const V x = vfma<V>(-w, u, xv[b]);
+                E[(int64_t)row * ld + col] = x;
                 const double ax = (double)fabs(x);
                 const uint64_t key = ((uint64_t)row << 32) | (uint32_t)col;
                 if (better(ax, key, bv, bk)) { bv = ax; bk = key; bs = (double)x; }
@@ -804,7 +800,7 @@ __device__ void sweep_body(const ProbDev *__restrict__ P, const ProbState *S, in
             new_tile<V, FNS>(P, K, u, R, C, ks[u], bv, bk, bs, (V *)smem_raw, nrec);
             TT_STAMP_ADD(rec, 10, 1);
             if (tid == 0) {
-                const gptr_t<Cand> c = as_global(K.cand) + (R * CT + C);
+                const gptr_t<Cand> c = as_global(K.cand) + idx;
                 c->v = bv; c->key = bk; c->sv = bs;
             }
             lds_barrier();
@@ -832,7 +828,7 @@ __device__ void sweep_body(const ProbDev *__restrict__ P, const ProbState *S, in
                 stored_tile_wave<V, 8>(K, ks[u], g, bv, bk, bs);
                 wave_best(bv, bk, bs);
                 if (lane == 0) {
-                    const gptr_t<Cand> c = as_global(K.cand) + (R * sh.CT[u] + C);
+                    const gptr_t<Cand> c = as_global(K.cand) + (sh.noff[u + 1] - sh.noff[u] + idx);
                     c->v = bv; c->key = bk; c->sv = bs;
                 }
 #ifdef TT_STAMPS
@@ -912,12 +908,13 @@ constexpr int CB = 8;              // candidates per lane in one round of loads
 // unfoldings' descriptors.
 struct CommitIn {
     KSweep ks[TT_MAX_D];
-    int ntl[TT_MAX_D];               // tiles (rook: blocks) each unfolding searched
     int rold[TT_MAX_D + 1];
     int stop;
     int err;                         // the state's error code, kept current here
     double tau;
     unsigned long long acc[3];       // alg_bytes, new_entries, pivoted
+    int off[2][TT_MAX_D + 1];        // the sweep's tile offsets (new, stored)
+    Cand prev[TT_MAX_D];             // best candidates of the sweep before
     KDev kd[TT_MAX_D];
     // the problem's fields the commit reads later, read up front
     int rook, r_max, fp32, rcap, hist_cap;
@@ -998,8 +995,9 @@ __device__ void commit_body(const ProbDev *__restrict__ P, ProbState *S, int swe
     }
     if (tid < nk) {
         load_words(ci.ks[tid], &S->ks[tid]);
-        ci.ntl[tid] = as_global(&S->sh.RT[tid])[0] * as_global(&S->sh.CT[tid])[0];
+        load_words(ci.prev[tid], &S->prev[tid]);
     }
+    if (tid >= 64 && tid < 64 + 2 * (TT_MAX_D + 1)) ci.off[0][tid - 64] = as_global(&S->sh.noff[0])[tid - 64];
     if (tid <= d) ci.rold[tid] = as_global(&S->r[par][tid])[0];
     if (tid == NTC - 1) {
         ci.stop = as_global(&S->stop)[0];
@@ -1035,7 +1033,7 @@ __device__ void commit_body(const ProbDev *__restrict__ P, ProbState *S, int swe
     // tiles, in every lane
     auto scan = [&](int us, double &bv, uint64_t &bk, double &bs) {
         const KDev &K = kd[us];
-        const int ntl = rook ? K.nrb * K.ncb : ci.ntl[us];
+        const int ntl = rook ? K.nrb * K.ncb : ci.off[0][us + 1] - ci.off[0][us] + ci.off[1][us + 1] - ci.off[1][us];
         bv = -1.0; bs = 0.0; bk = ~0ULL;
         if (rook && sl == 0) {
             // residuals the block searches looked at
@@ -1054,6 +1052,11 @@ __device__ void commit_body(const ProbDev *__restrict__ P, ProbState *S, int swe
             i0 += 64 * wpu * CB;
         }
         scan_cands(as_global((const Cand *)K.cand), i0, ntl, wpu, bv, bk, bs);
+        // stored entries that no pivot changed: their best is the last sweep's
+        if (!rook && sl == 0 && lane == 0 && !ks[us].apply &&
+            better(ci.prev[us].v, ci.prev[us].key, bv, bk)) {
+            bv = ci.prev[us].v; bk = ci.prev[us].key; bs = ci.prev[us].sv;
+        }
         wave_best(bv, bk, bs);
     };
 
@@ -1101,6 +1104,9 @@ __device__ void commit_body(const ProbDev *__restrict__ P, ProbState *S, int swe
         if (lane == 0) {
             if (sweep < ci.hist_cap) as_global((double *)K.hist)[sweep] = e;
             S->last_best[u] = e;
+            S->prev[u].v = bv;
+            S->prev[u].key = bk;
+            S->prev[u].sv = bs;
             if (over && !propose) S->capped = 1;
             if (propose && bs == 0.0) {
                 S->err = TT_ESINGULAR;
@@ -1119,7 +1125,7 @@ __device__ void commit_body(const ProbDev *__restrict__ P, ProbState *S, int swe
                 s_new[u] = 0;
                 s_piv[u] = s_rcnt[u];
             } else {
-                s_bytes[u] = live * sizeof(V) * (ks[u].apply ? 2ull : 1ull) + (all - nst * cst) * sizeof(V);
+                s_bytes[u] = (ks[u].apply ? live * sizeof(V) * 2ull : 0ull) + (all - nst * cst) * sizeof(V);
                 s_new[u] = all - nst * cst;
                 s_piv[u] = all;
             }
@@ -1205,7 +1211,7 @@ __device__ void commit_body(const ProbDev *__restrict__ P, ProbState *S, int swe
             S->sh.RTs[u] = RTs;
             S->sh.CTs[u] = CTs;
             nn = RT * CT - RTs * CTs;
-            ns = RTs * CTs;
+            ns = s_prop[u] ? RTs * CTs : 0;    // unchanged stored entries are not visited
         }
         // inclusive scans over the first 16 lanes (nk <= 15 carry counts)
         const int pn = row_scan_incl(nn), ps = row_scan_incl(ns);
@@ -1464,6 +1470,7 @@ __device__ void seeded_pivots(const ProbDev *__restrict__ P, ProbState *S, const
             ks.agam = 0;
             ks.apiv = 0.0;
             S->ks[u] = ks;
+            cand_none(S->prev[u]);           // nothing stored, nothing searched yet
             S->r[0][k] = m;
             S->r[1][k] = m;
             P->hm->r[k] = m;
