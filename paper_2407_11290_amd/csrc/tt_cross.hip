@@ -1249,8 +1249,9 @@ static int sampled_error_on(Problem &P, int64_t R, uint64_t seed, const ErrBufs 
     k_gen_idx<<<g, NT, 0, P.stream>>>(P.d, a, seed, R, b.idx);
     hipError_t e = launch_fn_eval<double>(P.fn.dev, R, b.idx, b.x, P.stream);
     if (e == hipSuccess) {
-        const int64_t waves = std::min<int64_t>(R, 65536);
-        k_tt_eval<<<(unsigned)((waves * 64 + NT - 1) / NT), NT, 0, P.stream>>>(a, P.d_cores, R, b.idx, b.y);
+        e = launch_tt_eval(a, P.d_cores, R, b.idx, b.y, P.stream);
+    }
+    if (e == hipSuccess) {
         k_err_partial<<<kErrParts, NT, 0, P.stream>>>(R, b.x, b.y, b.part);
         e = hipGetLastError();
     }
@@ -1520,9 +1521,7 @@ int tt_eval(tt_cross_h h, int64_t m, const int32_t *idx, double *out, int on_dev
         didx = (const int *)tmp_i;
         dout = (double *)tmp_o;
     }
-    const int64_t waves = std::min<int64_t>(m, 65536);
-    k_tt_eval<<<(unsigned)((waves * 64 + NT - 1) / NT), NT, 0, P.stream>>>(a, P.d_cores, m, didx, dout);
-    hipError_t e = hipGetLastError();
+    hipError_t e = launch_tt_eval(a, P.d_cores, m, didx, dout, P.stream);
     if (e == hipSuccess && !on_device) e = hipMemcpyAsync(out, dout, sizeof(double) * m, hipMemcpyDeviceToHost, P.stream);
     if (e == hipSuccess) e = hipStreamSynchronize(P.stream);
     if (tmp_i) (void)hipFree(tmp_i);

@@ -289,10 +289,9 @@ __device__ void stored_tile_wave(const KTile &K, const KSweep &ks, const TileGeo
 // a register move, no LDS round trip).  Every lane of the row must be active.
 template <int n> __device__ inline double row_bcast(double x)
 {
-    const long long b = __double_as_longlong(x);
-    const int lo = __builtin_amdgcn_update_dpp(0, (int)b, 0x150 + n, 0xf, 0xf, false);
-    const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), 0x150 + n, 0xf, 0xf, false);
-    return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
+    // one 64-bit move (the row broadcast is the DPP control that has one)
+    return __longlong_as_double(
+        __builtin_amdgcn_update_dpp(0ll, __double_as_longlong(x), 0x150 + n, 0xf, 0xf, true));
 }
 template <int n> __device__ inline float row_bcast(float x)
 {
@@ -3098,6 +3097,320 @@ static __global__ void __launch_bounds__(NT) k_tt_eval(TTArgs a, const double *_
         }
         if (gl == 0 && ok) out[t] = v;
     }
+}
+
+// The same values with the whole TT in LDS, one thread per index, its row
+// vector in registers: small ranks, where a lane group would leave most of
+// its lanes idle (ranks 1,2,1,7,1,1,1 kept 1.4 of 16 busy).  The terms of
+// every sum keep their order.
+constexpr int TE_LDS_RANK = 8;               // largest rank of this kernel
+constexpr int TE_LDS_MAX = 8192;             // doubles of cores it takes to LDS, at most
+
+static __global__ void __launch_bounds__(NT) k_tt_eval_lds(TTArgs a, const double *__restrict__ G, int64_t m,
+                                                           const int *__restrict__ idx, double *__restrict__ out)
+{
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    double *const sG = (double *)smem_raw;
+    const int d = a.d, len = (int)a.goff[d];
+    for (int e = threadIdx.x; e < len; e += NT) sG[e] = G[e];
+    __syncthreads();
+    const int64_t step = (int64_t)gridDim.x * NT;
+    for (int64_t t = (int64_t)blockIdx.x * NT + threadIdx.x; t < m; t += step) {
+        const int *ix = idx + t * d;
+        double v[TE_LDS_RANK];
+        v[0] = 1.0;
+#pragma unroll
+        for (int j = 1; j < TE_LDS_RANK; ++j) v[j] = 0.0;
+        for (int k = 0; k < d; ++k) {
+            const int ra = a.ranks[k], rb = a.ranks[k + 1];
+            const double *Gk = sG + a.goff[k] + ix[k] * rb;
+            const int sa = a.n[k] * rb;
+            double w[TE_LDS_RANK];
+#pragma unroll
+            for (int b = 0; b < TE_LDS_RANK; ++b) {
+                w[b] = 0.0;
+                if (b < rb) {
+#pragma unroll
+                    for (int j = 0; j < TE_LDS_RANK; ++j)
+                        if (j < ra) w[b] = __fma_rn(v[j], Gk[j * sa + b], w[b]);
+                }
+            }
+#pragma unroll
+            for (int b = 0; b < TE_LDS_RANK; ++b) v[b] = w[b];
+        }
+        out[t] = v[0];
+    }
+}
+
+// The same values for many indices, 16384 / RM of them per workgroup (RM >=
+// every rank), their row vectors in LDS.  At an inner mode with few enough
+// indices for a chunk to repeat them the workgroup sorts its indices by i_k
+// (a counting sort); a wavefront takes all of one i_k, sixteen at a time, and
+// multiplies their row vectors by the fibre G_k(:, i_k, :) on the matrix
+// cores: an FP64 matrix instruction adds its four terms in ascending order
+// with one rounding each, so the sums are those of the fma chain, bit for
+// bit.  A fibre is read from L2 once per chunk instead of once per index, the
+// next one while this one is used.  At the other inner modes a lane group
+// reads its own fibre for every index.
+constexpr int TE_V = 16384;                  // row-vector entries per workgroup
+__host__ __device__ constexpr int te_threads(int RM) { return RM == 16 ? 1024 : 512; }
+
+// Inclusive prefix sum over the wavefront (row shifts, then the row totals
+// carried by the row broadcasts).  Every lane must be active.
+__device__ inline int wave_scan_incl(int x)
+{
+    x = row_scan_incl(x);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);
+    return x;
+}
+
+// Entry b of index s's row vector, its low four bits turned by s: a column
+// read (one b, many s) would otherwise meet a few banks only.
+template <int RM> __device__ inline int te_slot(int s, int b) { return s * RM + (b ^ (s & 15)); }
+
+// One index's step at a mode, in place: the group's lane b holds column b of
+// the fibre in g, the row vector reaches the lanes by row broadcasts.  Blocks
+// of four terms, then the rest, with scalar branches on ra.
+template <int RM, int... B>
+__device__ inline void te_step(double *V, int s, int gl, const double *g, int ra, std::integer_sequence<int, B...>)
+{
+    double vv[RM / 16], acc = 0.0;
+#pragma unroll
+    for (int j = 0; j < RM / 16; ++j) vv[j] = V[te_slot<RM>(s, 16 * j + (gl & 15))];
+    ((void)[&] {
+        auto term = [&](auto c) {
+            constexpr int A = 4 * B + decltype(c)::value;
+            acc = __fma_rn(row_bcast<A & 15>(vv[A >> 4]), g[A], acc);
+        };
+        if (ra >= 4 * B + 4) {
+            term(std::integral_constant<int, 0>{});
+            term(std::integral_constant<int, 1>{});
+            term(std::integral_constant<int, 2>{});
+            term(std::integral_constant<int, 3>{});
+        } else if (ra > 4 * B) {
+            term(std::integral_constant<int, 0>{});
+            if (ra > 4 * B + 1) term(std::integral_constant<int, 1>{});
+            if (ra > 4 * B + 2) term(std::integral_constant<int, 2>{});
+        }
+    }(), ...);
+    V[te_slot<RM>(s, gl)] = acc;
+}
+
+typedef double dvec4 __attribute__((ext_vector_type(4)));
+
+// Steps at a mode by one wavefront, in place, for sixteen indices: rows s(p0
+// .. p0+15) below p1 of the order key, their fibre in g (lane l: rows
+// 4 kk + l/16, column 16 ct + l%16 of block (ct, kk)).  Rows past ra multiply
+// +0 by -1, so that the padding adds -0, which changes no value.  Every key
+// is read first, then every row vector: two LDS round trips.
+template <int RM>
+__device__ inline void te_block(double *V, const int *key, int p0, int p1, const double (&g)[RM / 16][RM / 4], int ra)
+{
+    const int lane = threadIdx.x & 63, lr = lane & 15, lq = lane >> 4;
+    const int s = key[min(p0 + lr, p1 - 1)];
+    int sr[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) sr[r] = key[min(p0 + 4 * r + lq, p1 - 1)];
+    double x[RM / 4];
+#pragma unroll
+    for (int kk = 0; kk < RM / 4; ++kk) x[kk] = V[te_slot<RM>(s, 4 * kk + lq)];
+    dvec4 acc[RM / 16];
+#pragma unroll
+    for (int ct = 0; ct < RM / 16; ++ct) acc[ct] = dvec4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int kk = 0; kk < RM / 4; ++kk) {
+        if (4 * kk >= ra) break;
+        const double xx = 4 * kk + lq < ra ? x[kk] : 0.0;
+#pragma unroll
+        for (int ct = 0; ct < RM / 16; ++ct)
+            acc[ct] = __builtin_amdgcn_mfma_f64_16x16x4f64(xx, g[ct][kk], acc[ct], 0, 0, 0);
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+        if (p0 + 4 * r + lq < p1) {
+#pragma unroll
+            for (int ct = 0; ct < RM / 16; ++ct) V[te_slot<RM>(sr[r], 16 * ct + lr)] = acc[ct][r];
+        }
+}
+
+template <int RM>
+static __global__ void __launch_bounds__(te_threads(RM)) k_tt_eval_sort(TTArgs a, const double *__restrict__ G,
+                                                                        int64_t m, const int *__restrict__ idx,
+                                                                        double *__restrict__ out)
+{
+    constexpr int TN = te_threads(RM), S = TE_V / RM, PP = S * RM / TN, NW = TN / 64;
+    constexpr int NBIN = S / 4;                  // indices of a mode that is sorted, at most
+    constexpr int BL = NBIN / 64;                // bins per lane of the scan
+    static_assert(S <= TN && RM % 16 == 0 && NBIN % 64 == 0 && S <= 65536, "one index per thread; whole DPP rows");
+    __shared__ double V[TE_V];
+    __shared__ int bins[2][NBIN + 1];
+    __shared__ int key[S];                       // i_k of a mode that is not sorted, else the sorted order
+    const int tid = threadIdx.x, lane = tid & 63, gid = tid / RM, gl = tid - gid * RM, d = a.d;
+    const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const gptr_t<const double> Gg = as_global(G);
+    const gptr_t<const int> IX = as_global(idx);
+    for (int e = tid; e < 2 * (NBIN + 1); e += TN) (&bins[0][0])[e] = 0;
+    for (int64_t base = (int64_t)blockIdx.x * S; base < m; base += (int64_t)gridDim.x * S) {
+        const int cnt = (int)min((int64_t)S, m - base);
+        const int64_t row = (base + min(tid, cnt - 1)) * d;
+        int i = IX[row + 1];
+        __syncthreads();                         // the previous chunk's reads are done
+        // mode 1: the row vector is G_1(i_1, :)
+        if (tid < S) key[tid] = IX[row];
+        __syncthreads();
+        {
+            const int rb = a.ranks[1], bb = min(gl, rb - 1);
+            double g[PP];
+#pragma unroll
+            for (int j = 0; j < PP; ++j) g[j] = Gg[(int64_t)key[gid * PP + j] * rb + bb];
+#pragma unroll
+            for (int j = 0; j < PP; ++j) V[te_slot<RM>(gid * PP + j, gl)] = __fma_rn(1.0, g[j], 0.0);
+        }
+        __syncthreads();                         // key is read
+        for (int k = 1; k + 1 < d; ++k) {
+            const int ra = a.ranks[k], rb = a.ranks[k + 1], n = a.n[k];
+            const gptr_t<const double> Gk = Gg + a.goff[k];
+            const int64_t sa = (int64_t)n * rb;
+            const int ik = i;
+            i = IX[row + k + 1];                 // the next mode's, in flight meanwhile
+            if (n <= NBIN) {
+                // counting sort: bin sizes (the buffer was cleared during the
+                // last mode's steps), their prefix sums, the order
+                int *const bin = bins[k & 1], *const other = bins[(k & 1) ^ 1];
+                const int rank = tid < cnt ? atomicAdd(&bin[ik], 1) : 0;
+                __syncthreads();
+                if (wid == 0) {
+                    int x[BL], sum = 0;
+#pragma unroll
+                    for (int j = 0; j < BL; ++j) {
+                        const int y = bin[lane * BL + j];
+                        x[j] = sum;
+                        sum += y;
+                    }
+                    const int before = wave_scan_incl(sum) - sum;
+#pragma unroll
+                    for (int j = 0; j < BL; ++j) bin[lane * BL + j] = before + x[j];
+                    if (lane == 63) bin[NBIN] = before + sum;
+                }
+                __syncthreads();
+                if (tid < cnt) key[bin[ik] + rank] = tid;
+                // units: all indices of one i_k, or every 2^lp-th sixteen of
+                // them where the mode has fewer indices than would feed the
+                // wavefronts
+                int lp = 0;
+                while ((n << lp) < 4 * NW) ++lp;
+                const int units = n << lp, lr = lane & 15, lq = lane >> 4;
+                // the lane's places in a fibre (a core of at most NBIN slices:
+                // 32-bit offsets from a scalar base)
+                uint32_t off[RM / 16][RM / 4];
+#pragma unroll
+                for (int ct = 0; ct < RM / 16; ++ct)
+#pragma unroll
+                    for (int kk = 0; kk < RM / 4; ++kk)
+                        off[ct][kk] = (uint32_t)(min(4 * kk + lq, ra - 1) * (n * rb) + min(16 * ct + lr, rb - 1));
+                auto fibre = [&](double (&g)[RM / 16][RM / 4], int t) {
+                    const gptr_t<const double> Gi = Gk + (min(t, units - 1) >> lp) * rb;
+#pragma unroll
+                    for (int ct = 0; ct < RM / 16; ++ct)
+#pragma unroll
+                        for (int kk = 0; kk < RM / 4; ++kk) {
+                            const double y = Gi[off[ct][kk]];
+                            g[ct][kk] = 4 * kk + lq < ra ? y : -1.0;
+                        }
+                };
+                auto unit = [&](int t, const double (&g)[RM / 16][RM / 4]) {
+                    const int is = t >> lp, p1 = __builtin_amdgcn_readfirstlane(bin[is + 1]);
+                    for (int p = __builtin_amdgcn_readfirstlane(bin[is]) + 16 * (t & ((1 << lp) - 1)); p < p1;
+                         p += 16 << lp)
+                        te_block<RM>(V, key, p, p1, g, ra);
+                };
+                double g[RM / 16][RM / 4];
+                fibre(g, wid);
+                __syncthreads();
+                for (int e = tid; e <= NBIN; e += TN) other[e] = 0;
+                if constexpr (RM <= 32) {
+                    double h[RM / 16][RM / 4];
+                    for (int t = wid; t < units; t += 2 * NW) {
+                        fibre(h, t + NW);
+                        unit(t, g);
+                        fibre(g, t + 2 * NW);
+                        if (t + NW < units) unit(t + NW, h);
+                    }
+                } else {                         // no registers for a second fibre
+                    for (int t = wid; t < units; t += NW) {
+                        unit(t, g);
+                        fibre(g, t + NW);
+                    }
+                }
+            } else {
+                int *const other = bins[(k & 1) ^ 1];
+                for (int e = tid; e <= NBIN; e += TN) other[e] = 0;
+                if (tid < S) key[tid] = ik;
+                __syncthreads();
+                const int bb = min(gl, rb - 1);
+                for (int p = gid * PP; p < min((gid + 1) * PP, cnt); ++p) {
+                    const gptr_t<const double> Gi = Gk + ((int64_t)key[p] * rb + bb);
+                    double g[RM];
+#pragma unroll
+                    for (int j = 0; j < RM; ++j) g[j] = Gi[min(j, ra - 1) * sa];
+                    te_step<RM>(V, p, gl, g, ra, std::make_integer_sequence<int, RM / 4>{});
+                }
+            }
+            __syncthreads();                     // row vectors, key and the cleared bins
+        }
+        // the last mode: G_d(:, i_d), one thread per index
+        if (tid < cnt) {
+            const int ra = a.ranks[d - 1], n = a.n[d - 1];
+            const gptr_t<const double> Gd = Gg + (a.goff[d - 1] + i);
+            double acc = 0.0;
+            for (int j0 = 0; j0 < ra; j0 += 16) {
+                double g[16];
+#pragma unroll
+                for (int j = 0; j < 16; ++j) g[j] = Gd[(int64_t)min(j0 + j, ra - 1) * n];
+#pragma unroll
+                for (int j = 0; j < 16; ++j)
+                    if (j0 + j < ra) acc = __fma_rn(V[te_slot<RM>(tid, j0 + j)], g[j], acc);
+            }
+            out[base + tid] = acc;
+        }
+        // the next chunk's first mode finds both bin buffers clear
+        for (int e = tid; e < 2 * (NBIN + 1); e += TN) (&bins[0][0])[e] = 0;
+    }
+}
+
+// Where the kernels cross, by measurement (us a call; host work about 15 of
+// each): the LDS kernel is level with the lane groups at 4000 indices of the
+// 6D Maxwellian (18.4 each), 18.5 against 21.1 at 10007 and 32 against 383 at
+// a million.  The sorting one, ranks 14-16 at n = 64: 54 against 62 at 65536,
+// 179 against 706 at a million; rank 25 at n = 1000 (not sorted): 88 against
+// 84 at 65536, 92 against 153 at 131072, 590 against 1037 at a million.  It
+// takes one chunk of 16384 / RM indices per CU at a time, 40 us each at d = 6:
+// the sorts, the matrix instructions and the fibre reads a quarter each.
+constexpr int64_t TE_LDS_MIN = 4096, TE_SORT_MIN = 65536, TE_SORT_MIN_WIDE = 98304;
+
+// Launch of the TT's values at m indices.
+inline hipError_t launch_tt_eval(const TTArgs &a, const double *G, int64_t m, const int *idx, double *out,
+                                 hipStream_t stream)
+{
+    if (m <= 0) return hipSuccess;
+    int rmax = 1;
+    for (int k = 1; k < a.d; ++k) rmax = std::max(rmax, a.ranks[k]);
+    const int64_t len = a.goff[a.d];
+    if (rmax <= TE_LDS_RANK && len <= TE_LDS_MAX && m >= TE_LDS_MIN) {
+        const unsigned g = (unsigned)std::min<int64_t>((m + NT - 1) / NT, 1024);
+        k_tt_eval_lds<<<g, NT, sizeof(double) * (size_t)len, stream>>>(a, G, m, idx, out);
+    } else if (m >= (rmax <= 16 ? TE_SORT_MIN : TE_SORT_MIN_WIDE)) {
+        const int S = TE_V / (rmax <= 16 ? 16 : rmax <= 32 ? 32 : 64);
+        const unsigned g = (unsigned)std::min<int64_t>((m + S - 1) / S, 1 << 20);
+        if (rmax <= 16) k_tt_eval_sort<16><<<g, te_threads(16), 0, stream>>>(a, G, m, idx, out);
+        else if (rmax <= 32) k_tt_eval_sort<32><<<g, te_threads(32), 0, stream>>>(a, G, m, idx, out);
+        else k_tt_eval_sort<64><<<g, te_threads(64), 0, stream>>>(a, G, m, idx, out);
+    } else {
+        const int64_t waves = std::min<int64_t>(m, 65536);
+        k_tt_eval<<<(unsigned)((waves * 64 + NT - 1) / NT), NT, 0, stream>>>(a, G, m, idx, out);
+    }
+    return hipGetLastError();
 }
 
 // The generating function at m multi-indices, in the arithmetic of V (the
