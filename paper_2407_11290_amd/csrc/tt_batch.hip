@@ -200,6 +200,7 @@ template <typename V> int Engine::launch_sweep(std::vector<int> &ids)
         bm.na = na;
         int off = 0;
         size_t lds = 0;
+        bool low = true;                         // ranks up to 16: the kernel without the code for more
         for (int a = 0; a < na; ++a) {
             Slot &s = slots[ids[c0 + a]];
             const Problem &Q = *s.Q;
@@ -211,10 +212,11 @@ template <typename V> int Engine::launch_sweep(std::vector<int> &ids)
             for (int u = 0; u < d - 1; ++u) {
                 const int k = u + 1;
                 const KDev &K = Q.hP.kd[u];
-                const int all = s.rub[k - 1] * K.RTp * s.rub[k + 1] * K.CTq;
-                const int st = std::min(all, s.rst[k - 1] * K.RTp * s.rst[k + 1] * K.CTq);
-                tot += (all - st) + (st + NT / 64 - 1) / (NT / 64);
-                lds = std::max(lds, sweep_lds_bytes(s.rub[k], K.TR, K.TC, sizeof(V)));
+                int nnew, nst;
+                low = low && s.rub[k] <= 16;
+                sweep_units(K, s.rub, s.rst, k, d - 1, nnew, nst);
+                tot += nnew + (nst + NT / 64 - 1) / (NT / 64);
+                lds = std::max(lds, sweep_lds_bytes(s.rub[k], K.TRn, K.TC, sizeof(V)));
             }
             bm.p[a] = (uint16_t)s.idx;
             bm.boff[a] = off;
@@ -224,7 +226,8 @@ template <typename V> int Engine::launch_sweep(std::vector<int> &ids)
             for (int k = 1; k <= d - 1; ++k) s.rub[k] = std::min(s.rub[k] + 1, Q.rc[k]);
         }
         bm.boff[na] = off;
-        k_sweep_b<V><<<off, NT, lds, stream>>>(dPa, bm);
+        if (low) k_sweep_b<V, true><<<off, NT, lds, stream>>>(dPa, bm);
+        else k_sweep_b<V, false><<<off, NT, lds, stream>>>(dPa, bm);
         k_commit_b<V><<<na, NTC, 0, stream>>>(dPa, bm);
         HIPCHK(hipGetLastError());
     }

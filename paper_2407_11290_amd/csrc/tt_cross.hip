@@ -317,11 +317,11 @@ int Problem::allocate()
         // (the larger of the Hilbert kernel's and the general one's)
         hipFuncAttributes fa, fh;
         if (fp32) {
-            HIPCHK(hipFuncGetAttributes(&fa, reinterpret_cast<const void *>(&k_sweep<float, 0>)));
-            HIPCHK(hipFuncGetAttributes(&fh, reinterpret_cast<const void *>(&k_sweep<float, TT_FN_HILBERT>)));
+            HIPCHK(hipFuncGetAttributes(&fa, reinterpret_cast<const void *>(&k_sweep<float, 0, false>)));
+            HIPCHK(hipFuncGetAttributes(&fh, reinterpret_cast<const void *>(&k_sweep<float, TT_FN_HILBERT, false>)));
         } else {
-            HIPCHK(hipFuncGetAttributes(&fa, reinterpret_cast<const void *>(&k_sweep<double, 0>)));
-            HIPCHK(hipFuncGetAttributes(&fh, reinterpret_cast<const void *>(&k_sweep<double, TT_FN_HILBERT>)));
+            HIPCHK(hipFuncGetAttributes(&fa, reinterpret_cast<const void *>(&k_sweep<double, 0, false>)));
+            HIPCHK(hipFuncGetAttributes(&fh, reinterpret_cast<const void *>(&k_sweep<double, TT_FN_HILBERT, false>)));
         }
         lds_static = (int)std::max(fa.sharedSizeBytes, fh.sharedSizeBytes);
     }
@@ -413,20 +413,29 @@ int Problem::allocate()
                 else TR /= 2;
             }
         }
-        std::vector<int> rs, rl, rb, cs, cl, cb;
+        // new-entry tiles are at most NEW_ROWS high: a workgroup's work is a
+        // chain of phases, and tall ones left most of the chip idle (3D, n =
+        // 1000: 128 tiles of 256 x 64 a sweep)
+        const int TRn = std::min(TR, NEW_ROWS);
+        std::vector<int> rs, rl, rb, cs, cl, cb, ms, ml, mb;
         mode_tiles(n[k - 1], grid[k - 1], TR, rs, rl, rb);
+        mode_tiles(n[k - 1], grid[k - 1], TRn, ms, ml, mb);
         mode_tiles(n[k], grid[k], TC, cs, cl, cb);
         if (!rook && sweep_lds_bytes(rc[k], TR, TC, w) + lds_static > (size_t)lds_limit)
             return set_err(TT_EINVAL, "tile %dx%d with rank cap %d needs more LDS than a workgroup has (%d B)",
                            TR, TC, rc[k], lds_limit);
         K.RTp = (int)rs.size();
         K.CTq = (int)cs.size();
+        K.RTn = (int)ms.size();
+        K.TRn = TRn;
         K.TR = TR;
         K.TC = TC;
+        K.smax = 0;
+        while ((64 << K.smax) <= TR) ++K.smax;
         tileTR[u] = TR;
         tileTC[u] = TC;
         int *tabs;
-        if ((st = dalloc((void **)&tabs, sizeof(int) * 3 * (rs.size() + cs.size()))) != TT_OK) return st;
+        if ((st = dalloc((void **)&tabs, sizeof(int) * (3 * (rs.size() + cs.size()) + 2 * ms.size()))) != TT_OK) return st;
         std::vector<int> all;
         all.insert(all.end(), rs.begin(), rs.end());
         all.insert(all.end(), rl.begin(), rl.end());
@@ -434,10 +443,13 @@ int Problem::allocate()
         all.insert(all.end(), cs.begin(), cs.end());
         all.insert(all.end(), cl.begin(), cl.end());
         all.insert(all.end(), cb.begin(), cb.end());
+        all.insert(all.end(), ms.begin(), ms.end());
+        all.insert(all.end(), ml.begin(), ml.end());
         HIPCHK(hipMemcpy(tabs, all.data(), sizeof(int) * all.size(), hipMemcpyHostToDevice));
         const int R = K.RTp, Cc = K.CTq;
         K.rt_start = tabs; K.rt_len = tabs + R; K.rt_blk = tabs + 2 * R;
         K.ct_start = tabs + 3 * R; K.ct_len = tabs + 3 * R + Cc; K.ct_blk = tabs + 3 * R + 2 * Cc;
+        K.nt_start = K.ct_blk + Cc; K.nt_len = K.nt_start + K.RTn;
         const int rk = rc[k];
         if (rook) {
             // factors W (rows x rank) and U (rank x columns) instead of the residual
@@ -471,7 +483,7 @@ int Problem::allocate()
         if ((st = dalloc((void **)&K.piv64, sizeof(double) * rk)) != TT_OK) return st;
         if ((st = dalloc((void **)&K.Wp64, sizeof(double) * rcmax * rcmax)) != TT_OK) return st;
         if ((st = dalloc((void **)&K.Up64, sizeof(double) * rcmax * rcmax)) != TT_OK) return st;
-        K.cand_cap = rook ? K.nrb * K.ncb : (rc[k - 1] * K.RTp) * (rc[k + 1] * K.CTq);
+        K.cand_cap = rook ? K.nrb * K.ncb : rc[k - 1] * ((K.RTp << K.smax) + K.RTn) * (rc[k + 1] * K.CTq) + 1;
         if ((st = dalloc((void **)&K.cand, sizeof(Cand) * K.cand_cap)) != TT_OK) return st;
         if ((st = dalloc((void **)&K.hist, sizeof(double) * hist_cap)) != TT_OK) return st;
         cores_cap += (int64_t)rc[k - 1] * n[k - 1] * rc[k];
@@ -503,8 +515,8 @@ int Problem::allocate()
     for (int u = 0; u < d - 1; ++u) {
         const KDev &K = H.kd[u];
         KTile &T = H.kt[u];
-        T.nk = K.nk; T.nk1 = K.nk1; T.ld = K.ld; T.RTp = K.RTp; T.CTq = K.CTq; T.TR = K.TR; T.TC = K.TC;
-        T.pad = 0;
+        T.nk = K.nk; T.nk1 = K.nk1; T.ld = K.ld; T.RTp = K.RTp; T.CTq = K.CTq; T.RTn = K.RTn;
+        T.TRn = K.TRn; T.TC = K.TC; T.TR = K.TR; T.pad = 0; T.nt_start = K.nt_start; T.nt_len = K.nt_len;
         T.rt_start = K.rt_start; T.rt_len = K.rt_len; T.ct_start = K.ct_start; T.ct_len = K.ct_len;
         T.E = K.E; T.rpiv = K.rpiv; T.cpiv = K.cpiv; T.rho = K.rho; T.gam = K.gam; T.piv = K.piv;
         T.Ifull = K.Ifull; T.Jfull = K.Jfull;
@@ -517,10 +529,12 @@ int Problem::allocate()
     std::memset(&H.sh0, 0, sizeof H.sh0);
     for (int u = 0, acc = 0; u < d - 1; ++u) {
         const KDev &K = H.kd[u];
-        H.sh0.RT[u] = H.sh0.RTs[u] = K.RTp;
+        H.sh0.RT[u] = H.sh0.RTs[u] = K.RTn;
         H.sh0.CT[u] = H.sh0.CTs[u] = K.CTq;
         H.sh0.soff[u] = acc;
-        acc += K.RTp * K.CTq;
+        H.sh0.lsp[u] = stored_split(K.RTp * K.CTq, d - 1, K.smax);
+        H.sh0.ntl[u] = (K.RTp * K.CTq) << H.sh0.lsp[u];
+        acc += H.sh0.ntl[u];
         H.sh0.soff[u + 1] = acc;
     }
     if ((st = dalloc((void **)&dP, sizeof(ProbDev))) != TT_OK) return st;
@@ -652,16 +666,18 @@ template <typename V> int Problem::launch_ahead()
         a.S = hP.S;
         int units = 0;
         size_t lds = 0;
+        bool low = true;
         for (int u = 0; u < nk; ++u) {
+            low = low && rub[u + 1] <= 16;
             const int k = u + 1;
             const KDev &K = hP.kd[u];
-            const int all = rub[k - 1] * K.RTp * rub[k + 1] * K.CTq;
+            int nnew, nst;
+            sweep_units(K, rub, rst, k, nk, nnew, nst);
             // the commit's first round of candidates: at most this many
             a.cand[u] = K.cand;
-            a.ntl_max[u] = rook ? K.nrb * K.ncb : all;
-            const int st = std::min(all, rst[k - 1] * K.RTp * rst[k + 1] * K.CTq);
-            units += (all - st) + (st + NT / 64 - 1) / (NT / 64);
-            lds = std::max(lds, sweep_lds_bytes(rub[k], K.TR, K.TC, sizeof(V)));
+            a.ntl_max[u] = rook ? K.nrb * K.ncb : rub[k - 1] * (K.RTn + (K.RTp << K.smax)) * rub[k + 1] * K.CTq + 1;
+            units += nnew + (nst + NT / 64 - 1) / (NT / 64);
+            lds = std::max(lds, sweep_lds_bytes(rub[k], K.TRn, K.TC, sizeof(V)));
         }
         // one workgroup per expected work unit (new tiles one each, stored
         // tiles four each); the kernel strides over the exact unit count it
@@ -670,7 +686,9 @@ template <typename V> int Problem::launch_ahead()
         for (int k = 0; k <= d; ++k) rst[k] = rub[k];
         // the Hilbert tensor gets a kernel built for it alone (fewer
         // registers, more workgroups resident); the others share one
-        auto kern = hil ? k_sweep<V, TT_FN_HILBERT> : k_sweep<V, 0>;
+        // and ranks up to 16 one without the code for more
+        auto kern = low ? (hil ? k_sweep<V, TT_FN_HILBERT, true> : k_sweep<V, 0, true>)
+                        : (hil ? k_sweep<V, TT_FN_HILBERT, false> : k_sweep<V, 0, false>);
         if (rook) {
             // factors: one thread per superblock row and column (bounded by
             // the ranks this sweep can have), then one workgroup per block

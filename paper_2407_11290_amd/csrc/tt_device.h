@@ -211,9 +211,12 @@ struct KDev {
     int rowcap, colcap;           // capacity of the stored superblock
     int ld;                       // row pitch of E in entries (colcap padded off powers of two)
     int rk_cap;                   // pivot capacity of this unfolding
-    int RTp, CTq;                 // row tiles per prefix, column tiles per suffix
-    int TR, TC;                   // largest tile extent (LDS/thread layout)
-    const int *rt_start, *rt_len, *rt_blk;    // per row tile within a prefix
+    int RTp, CTq;                 // stored row tiles per prefix, column tiles per suffix
+    int RTn, TRn;                 // new-entry row tiles per prefix and their largest height
+    int TR, TC;                   // largest extent of a stored tile (its width is any tile's)
+    int smax;                     // log2 of the parts a stored tile can be searched in
+    const int *rt_start, *rt_len, *rt_blk;    // per stored row tile within a prefix
+    const int *nt_start, *nt_len;             // per new-entry row tile within a prefix
     const int *ct_start, *ct_len, *ct_blk;    // per column tile within a suffix
     void *E;                      // residual / frozen factors, rowcap x colcap, row-major, pitch ld
     uint8_t *rpiv, *cpiv;         // z+1 on the row / column of pivot z, else 0 (padded to whole words)
@@ -242,8 +245,8 @@ struct KDev {
 // its neighbours' index-tuple arrays; kept apart and small, so that a search
 // workgroup loads every unfolding's copy in its first round of loads.
 struct KTile {
-    int nk, nk1, ld, RTp, CTq, TR, TC, pad;
-    const int *rt_start, *rt_len, *ct_start, *ct_len;
+    int nk, nk1, ld, RTp, CTq, RTn, TRn, TC, TR, pad;
+    const int *rt_start, *rt_len, *nt_start, *nt_len, *ct_start, *ct_len;
     void *E;
     const uint8_t *rpiv, *cpiv;
     const int *rho, *gam;
@@ -276,25 +279,40 @@ struct KSweep {
 };
 
 // Tiles per unfolding of one sweep, split into new-entry tiles and stored
-// tiles, with the running offsets of both kinds over the unfoldings.
+// tiles, with the running offsets of both kinds over the unfoldings.  RT, RTs
+// count rows of new-entry tiles (all, and those over stored rows).
 //
 // An unfolding that committed nothing has no pivot to apply, and its masks
 // are as they were: its stored region is the superblock of the sweep before,
-// entry for entry, so the best candidate of that sweep (ProbState::prev) is
-// the region's and none of its tiles is visited (soff counts none).
+// entry for entry, so the best candidate of that sweep is the region's and
+// none of its tiles is visited (soff counts none).
 // Candidates lie densely per unfolding: its new tiles in order, then its
-// stored tiles.
+// stored tiles or, where they are not visited, their best of the sweep
+// before (written by its commit).
 struct SweepShape {
     int RT[TT_MAX_D], CT[TT_MAX_D], RTs[TT_MAX_D], CTs[TT_MAX_D];
+    int lsp[TT_MAX_D];            // a stored tile is 2^lsp units (see stored_split)
+    int ntl[TT_MAX_D];            // candidates of the sweep
     int noff[TT_MAX_D + 1], soff[TT_MAX_D + 1];
 };
 constexpr int SHAPE_WORDS = (int)(sizeof(SweepShape) / sizeof(int));
+
+// Parts (2^l) a sweep searches each stored tile of an unfolding in: tall
+// tiles stream best when there are many, but a wavefront takes its tile's
+// rows one batch after another (256 rows about 50 us), so while the tiles of
+// all nk unfoldings would not give every CU sixteen wavefronts they are cut,
+// down to 32 rows.
+__host__ __device__ inline int stored_split(int tiles, int nk, int smax)
+{
+    int l = 0;
+    while (l < smax && (((int64_t)tiles * nk) << l) < 4096) ++l;
+    return l;
+}
 
 struct ProbState {
     int r[2][TT_MAX_D + 1];       // committed ranks, double-buffered by sweep parity
     KSweep ks[TT_MAX_D];
     SweepShape sh;                // tile counts of the sweep ks describes
-    Cand prev[TT_MAX_D];          // best candidate of the superblock searched last
     int stop, capped, err, sweeps;
     unsigned long long pivoted;
     unsigned long long alg_bytes;   // algorithmic residual traffic of the tile launches

@@ -157,16 +157,29 @@ __host__ __device__ inline size_t sweep_lds_bytes(int rk, int TR, int TC, size_t
     return ((size_t)rk * (TR + TC) + (size_t)rk * (rk > 0 ? rk - 1 : 0)) * w;
 }
 
+// Tiles of unfolding k in a sweep whose superblock has ranks up to rub and
+// whose stored region those of rst: new-entry tiles and parts of stored tiles.
+inline void sweep_units(const KDev &K, const int *rub, const int *rst, int k, int nk, int &nnew, int &nst)
+{
+    const int all = rub[k - 1] * K.RTn * rub[k + 1] * K.CTq;
+    nnew = all - std::min(all, rst[k - 1] * K.RTn * rst[k + 1] * K.CTq);
+    nst = std::min(rub[k - 1], rst[k - 1]) * K.RTp * std::min(rub[k + 1], rst[k + 1]) * K.CTq;
+    nst <<= stored_split(nst, nk, K.smax);
+}
+
 // ---------------------------------------------------------------------------
 // Search tiles.
 // ---------------------------------------------------------------------------
+constexpr int NEW_ROWS = 128;                 // largest height of a new-entry tile
+
 struct TileGeom {
     int u, R, C;                  // unfolding, row tile, column tile
     int ik0, nrows, ik10, ncols;  // i_k / i_{k+1} ranges of the tile
     int row0, col0, p, q;         // first row / column position, prefix / suffix
 };
 
-__device__ inline TileGeom tile_geom(const KTile &K, int u, int R, int C)
+// Part `part` of 2^lsp of stored tile (R, C); nrows may come out as 0.
+__device__ inline TileGeom tile_geom(const KTile &K, int u, int R, int C, int part, int lsp)
 {
     TileGeom g;
     g.u = u; g.R = R; g.C = C;
@@ -174,7 +187,9 @@ __device__ inline TileGeom tile_geom(const KTile &K, int u, int R, int C)
     const int t = R - g.p * K.RTp;
     g.q = C / K.CTq;
     const int tc = C - g.q * K.CTq;
-    g.ik0 = K.rt_start[t]; g.nrows = K.rt_len[t];
+    const int h = (K.TR + (1 << lsp) - 1) >> lsp;
+    g.ik0 = K.rt_start[t] + part * h;
+    g.nrows = max(min(K.rt_len[t] - part * h, h), 0);
     g.ik10 = K.ct_start[tc]; g.ncols = K.ct_len[tc];
     g.row0 = g.p * K.nk + g.ik0;
     g.col0 = g.q * K.nk1 + g.ik10;
@@ -310,18 +325,19 @@ __device__ inline int row_scan_incl(int x)
     return x;
 }
 
-// Factor solves of a new-entry tile for ranks rk <= RK <= 16: a 16-lane
-// group per row (column), lane z holding factor z; at step z' the finished
-// factor z' reaches the lanes z > z' of its group by a row broadcast.
+// Factor solves of a new-entry tile, for factors zb .. zb+RK-1 (RK <= 16)
+// whose chains have taken the ones below zb already: a 16-lane group per row
+// (column), lane z holding factor zb + z; at step z' the finished factor
+// reaches the lanes z > z' of its group by a row broadcast.
 //   row i:    w_z = W_raw(i, z) - sum_{z'<z} w_z' U(z', gamma_z)
 //   column j: e_z = X(rho_z, j) - sum_{z'<z} W(rho_z, z') e_z' / p_z'
 // each sum in ascending z'.  Steps past rk - 1 change no lane below rk.
 template <typename V, int... Z>
-__device__ inline void row_steps(V &w, const V *Gr, int zl, bool ok, std::integer_sequence<int, Z...>)
+__device__ inline void row_steps(V &w, const V *Gr, int zb, int zl, bool ok, std::integer_sequence<int, Z...>)
 {
     ((void)[&] {
         const V wz = row_bcast<Z>(w);
-        if (ok && zl > Z) w = vfma<V>(-wz, Gr[tri(Z, zl)], w);
+        if (ok && zl > Z) w = vfma<V>(-wz, Gr[tri(zb + Z, zb + zl)], w);
     }(), ...);
 }
 // The quotient e_z' / p_z' of a column step comes from the pivot's correctly
@@ -339,13 +355,13 @@ template <typename V> __device__ inline V div_by_recip(V e, V p, V r)
 // spare for the pivots and reciprocals the compiler reads ahead), else the
 // division itself.
 template <typename V, bool RECIP, int... Z>
-__device__ inline void col_steps(V &u, const V *Gc, const V *s_piv, const V *s_rpiv, int zl, bool ok,
+__device__ inline void col_steps(V &u, const V *Gc, const V *s_piv, const V *s_rpiv, int zb, int zl, bool ok,
                                  std::integer_sequence<int, Z...>)
 {
     ((void)[&] {
         const V uz = row_bcast<Z>(u);
-        const V uu = RECIP ? div_by_recip<V>(uz, s_piv[Z], s_rpiv[Z]) : uz / s_piv[Z];
-        if (ok && zl > Z) u = vfma<V>(-Gc[tri(Z, zl)], uu, u);
+        const V uu = RECIP ? div_by_recip<V>(uz, s_piv[zb + Z], s_rpiv[zb + Z]) : uz / s_piv[zb + Z];
+        if (ok && zl > Z) u = vfma<V>(-Gc[tri(zb + Z, zb + zl)], uu, u);
     }(), ...);
 }
 
@@ -356,32 +372,112 @@ __device__ inline void col_steps(V &u, const V *Gc, const V *s_piv, const V *s_r
 template <typename V, int RK, bool RECIP>
 __device__ inline void solves_lg(gptr_t<V> E, int64_t ld, const TileGeom &g, V *Wt, V *Ut, const V *Gr,
                                  const V *Gc, const V *s_piv, const V *s_rpiv, const int *s_rho, const int *s_gam,
-                                 int TRm, int TCm, int rk, int nrw, int ncw, const uint8_t *s_rp,
+                                 int TRm, int TCm, int zb, int rk, int nrw, int ncw, const uint8_t *s_rp,
                                  const uint8_t *s_cp)
 {
-    const int tid = threadIdx.x, zl = tid & 15, gid = tid >> 4;
+    const int tid = threadIdx.x, zl = tid & 15, z = zb + zl, gid = tid >> 4;
     constexpr int ngroups = NT / 16;
     using Steps = std::make_integer_sequence<int, RK - 1>;
     for (int base = 0; base < nrw; base += ngroups) {
         const int ii = base + gid;
-        const bool ok = ii < nrw && zl < rk;
-        V w = ok ? Wt[zl * TRm + ii] : (V)0;
-        row_steps<V>(w, Gr, zl, ok, Steps{});
+        const bool ok = ii < nrw && z < rk;
+        V w = ok ? Wt[z * TRm + ii] : (V)0;
+        row_steps<V>(w, Gr, zb, zl, ok, Steps{});
         if (ok) {
-            Wt[zl * TRm + ii] = w;
-            const int gz = s_gam[zl];
+            Wt[z * TRm + ii] = w;
+            const int gz = s_gam[z];
             if (!s_rp[ii] && gz >= g.col0 && gz < g.col0 + g.ncols) E[(int64_t)(g.row0 + ii) * ld + gz] = w;
         }
     }
     for (int base = 0; base < ncw; base += ngroups) {
         const int jj = base + gid;
-        const bool ok = jj < ncw && zl < rk;
-        V u = ok ? Ut[zl * TCm + jj] : (V)0;
-        col_steps<V, RECIP>(u, Gc, s_piv, s_rpiv, zl, ok, Steps{});
+        const bool ok = jj < ncw && z < rk;
+        V u = ok ? Ut[z * TCm + jj] : (V)0;
+        col_steps<V, RECIP>(u, Gc, s_piv, s_rpiv, zb, zl, ok, Steps{});
         if (ok) {
-            const int rz = s_rho[zl];
+            const int rz = s_rho[z];
             if (!s_cp[jj] && rz >= g.row0 && rz < g.row0 + g.nrows) E[(int64_t)rz * ld + g.col0 + jj] = u;
-            Ut[zl * TCm + jj] = u / s_piv[zl];
+            Ut[z * TCm + jj] = u / s_piv[z];
+        }
+    }
+}
+
+// One matrix instruction adds four products to each accumulator, in ascending
+// order with one rounding each (FP32 and FP64, subnormals, signed zeros and
+// non-finite values included): the fma chain's bits.  Lane l = 16 lq + lr
+// gives row lr, term lq of the left factor, term lq, column lr of the right
+// one, and holds rows row(lq, 0..3) of column lr of the result.
+template <typename V> struct Mfma;
+template <> struct Mfma<double> {
+    typedef double vec __attribute__((ext_vector_type(4)));
+    __device__ static int row(int lq, int r) { return 4 * r + lq; }
+    __device__ static vec mac(double a, double b, vec c) { return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0); }
+};
+template <> struct Mfma<float> {
+    typedef float vec __attribute__((ext_vector_type(4)));
+    __device__ static int row(int lq, int r) { return 4 * lq + r; }
+    __device__ static vec mac(float a, float b, vec c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
+};
+
+// x minus the products W(i, z) U(z, j), z = 0 .. rk-1 in order, on a 16 x 16
+// block: w (u) points at the lane's row (column) of the factors, wp (up)
+// values from one z to the next.  Terms past rk multiply +0 by -1: they add
+// -0, which changes no value.  Sixteen terms' factors are read at a time.
+template <typename V>
+__device__ inline typename Mfma<V>::vec eliminate(typename Mfma<V>::vec x, const V *w, int wp, const V *u, int up, int rk,
+                                                  int lq)
+{
+    for (int z0 = 0; z0 < rk; z0 += 16) {
+        V a[4], b[4];
+#pragma unroll
+        for (int m = 0; m < 4; ++m) {
+            const int z = min(z0 + 4 * m + lq, rk - 1);
+            a[m] = w[z * wp];
+            b[m] = u[z * up];
+        }
+#pragma unroll
+        for (int m = 0; m < 4; ++m) {
+            if (z0 + 4 * m >= rk) break;
+            const bool in = z0 + 4 * m + lq < rk;
+            x = Mfma<V>::mac(in ? -a[m] : (V)0, in ? b[m] : (V)-1, x);
+        }
+    }
+    return x;
+}
+
+// Takes the finished factors below zb (a multiple of 16) out of the raw
+// factors zb .. zb+15 of new rows (columns), in ascending order: 16 x 16
+// blocks of rows x factors (factors x columns), a wavefront each.
+template <typename V>
+__device__ inline void solves_below(V *Wt, V *Ut, const V *Gr, const V *Gc, int TRm, int TCm, int zb, int rk, int nrw,
+                                    int ncw)
+{
+    const int lane = threadIdx.x & 63, lr = lane & 15, lq = lane >> 4;
+    const int nbw = (nrw + 15) >> 4, nb = nbw + ((ncw + 15) >> 4), z = min(zb + lr, rk - 1);
+    for (int b = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); b < nb; b += NT / 64) {
+        typename Mfma<V>::vec x;
+        if (b < nbw) {
+            const int ia = min(16 * b + lr, nrw - 1);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) x[r] = Wt[z * TRm + min(16 * b + Mfma<V>::row(lq, r), nrw - 1)];
+#pragma unroll 4
+            for (int zp = lq; zp < zb; zp += 4) x = Mfma<V>::mac(-Wt[zp * TRm + ia], Gr[tri(zp, z)], x);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int ii = 16 * b + Mfma<V>::row(lq, r);
+                if (ii < nrw && zb + lr < rk) Wt[z * TRm + ii] = x[r];
+            }
+        } else {
+            const int j0 = 16 * (b - nbw), jb = min(j0 + lr, ncw - 1);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) x[r] = Ut[min(zb + Mfma<V>::row(lq, r), rk - 1) * TCm + jb];
+#pragma unroll 4
+            for (int zp = lq; zp < zb; zp += 4) x = Mfma<V>::mac(-Gc[tri(zp, z)], Ut[zp * TCm + jb], x);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int zr = zb + Mfma<V>::row(lq, r);
+                if (zr < rk && j0 + lr < ncw) Ut[zr * TCm + jb] = x[r];
+            }
         }
     }
 }
@@ -394,7 +490,9 @@ __device__ inline void solves_lg(gptr_t<V> E, int64_t ld, const TileGeom &g, V *
 //   row i:    e_z = X(i, gamma_z); for z' < z: e_z -= e_z' * U(z', gamma_z)   -> W(i, z)
 //   column j: e_z = X(rho_z, j);   for z' < z: e_z -= W(rho_z, z') * e_z'/p_z' -> p_z U(z, j)
 // and the frozen pivot columns / rows of the tile receive those values.
-template <typename V, int FNS>
+// LOW: rk <= 16, and nothing of the code for more (its registers cost the
+// search of small ranks 0.4 us a tile).
+template <typename V, int FNS, bool LOW>
 __device__ void new_tile(const ProbDev *__restrict__ P, const KTile &K, int u, int R, int C, const KSweep &ks,
                          double &bv, uint64_t &bk, double &bs, V *sm, unsigned long long *rec)
 {
@@ -407,8 +505,8 @@ __device__ void new_tile(const ProbDev *__restrict__ P, const KTile &K, int u, i
     // together with the staging below.
     const gptr_t<const int> Ipre = as_global(K.Ipre);
     const gptr_t<const int> Jsuf = as_global(K.Jsuf);
-    const int RTp = K.RTp, CTq = K.CTq;
-    const int tp = R / RTp, tt = R - tp * RTp, tq = C / CTq, ttc = C - tq * CTq;
+    const int RTn = K.RTn, CTq = K.CTq;
+    const int tp = R / RTn, tt = R - tp * RTn, tq = C / CTq, ttc = C - tq * CTq;
     // row (column) blocks are whole prefixes (suffixes), so whether the tile's
     // rows (columns) were stored follows from the prefix (suffix) index alone
     const bool rows_old = __builtin_amdgcn_readfirstlane(tp * K.nk < ks.nr_st ? 1 : 0) != 0;
@@ -418,7 +516,7 @@ __device__ void new_tile(const ProbDev *__restrict__ P, const KTile &K, int u, i
 #endif
     TileGeom g;
     g.u = u; g.R = R; g.C = C; g.p = tp; g.q = tq;
-    g.ik0 = K.rt_start[tt]; g.nrows = K.rt_len[tt];
+    g.ik0 = K.nt_start[tt]; g.nrows = K.nt_len[tt];
     g.ik10 = K.ct_start[ttc]; g.ncols = K.ct_len[ttc];
     const gptr_t<V> E = as_global((V *)K.E);
     const gptr_t<const int> rho = as_global((const int *)K.rho), gam = as_global((const int *)K.gam);
@@ -430,13 +528,11 @@ __device__ void new_tile(const ProbDev *__restrict__ P, const KTile &K, int u, i
     __shared__ V s_piv[TT_MAX_RANK], s_rpiv[TT_MAX_RANK];   // pivots and their reciprocals
     __shared__ uint8_t s_rp[TT_TILE_ROWS_MAX], s_cp[TT_TILE_ROWS_MAX];
     const int npre = k - 1, nsuf = d - k - 1, nj = d - k;
-    const int TRm = K.TR, TCm = K.TC, ntri = rk * (rk - 1) / 2;
+    const int TRm = K.TRn, TCm = K.TC, ntri = rk * (rk - 1) / 2;
     V *Wt = sm;                                // Wt[z*TRm+ii] = W(row, z)
     V *Ut = Wt + (int64_t)rk * TRm;            // Ut[z*TCm+jj] = U(z, col)
     V *Gr = Ut + (int64_t)rk * TCm;            // U(z', gamma_z), z' < z
     V *Gc = Gr + ntri;                         // W(rho_z, z'), z' < z
-    const int TCt = K.TC, rpp = NT / TCt;
-    const int tr = tid / TCt, tcol = tid - tr * TCt;
     // one round of loads: the neighbours' tuples, the pivots (rk <= NT: one
     // per thread) and, for Hilbert, the words of the pivots' tuples, every
     // value in flight before the first is stored (a store waits for its load,
@@ -503,6 +599,7 @@ __device__ void new_tile(const ProbDev *__restrict__ P, const KTile &K, int u, i
     // loads per thread.
     static_assert(TT_TILE_ROWS_MAX <= NT, "one tile row and one tile column per thread");
     constexpr int UL = 4;
+    static_assert(16 * 16 <= NT, "the triangles of 16 pivots in one pass");
     const gptr_t<const uint8_t> rpiv = as_global((const uint8_t *)K.rpiv), cpiv = as_global((const uint8_t *)K.cpiv);
     const int nw = rk * g.nrows, nu = rk * g.ncols;
     const int tzp = tid / max(rk, 1), tz = tid - tzp * rk;  // the thread's triangle entry (zp, z) in the first pass
@@ -571,7 +668,7 @@ __device__ void new_tile(const ProbDev *__restrict__ P, const KTile &K, int u, i
             }
         }
     } else {
-        for (int e = tid + NT; e < rk * rk; e += NT) {
+        for (int e = tid + NT; !LOW && e < rk * rk; e += NT) {
             const int zp = e / rk, z = e - zp * rk;
             if (zp < z) Gr[tri(zp, z)] = E[(int64_t)s_rho[zp] * ld + s_gam[z]] / s_piv[zp];
         }
@@ -595,7 +692,7 @@ __device__ void new_tile(const ProbDev *__restrict__ P, const KTile &K, int u, i
         }
     }
     if (cols_old) {
-        for (int e0 = tid + UL * NT; e0 < nu; e0 += UL * NT) {
+        for (int e0 = tid + UL * NT; !(LOW && 16 * 64 <= UL * NT) && e0 < nu; e0 += UL * NT) {
             V x[UL];
 #pragma unroll
             for (int j = 0; j < UL; ++j) {
@@ -611,7 +708,7 @@ __device__ void new_tile(const ProbDev *__restrict__ P, const KTile &K, int u, i
             }
         }
     } else {
-        for (int e = tid + NT; e < rk * rk; e += NT) {
+        for (int e = tid + NT; !LOW && e < rk * rk; e += NT) {
             const int zp = e / rk, z = e - zp * rk;
             if (zp < z) Gc[tri(zp, z)] = E[(int64_t)s_rho[z] * ld + s_gam[zp]];
         }
@@ -636,99 +733,70 @@ __device__ void new_tile(const ProbDev *__restrict__ P, const KTile &K, int u, i
     }
     __syncthreads();
     TT_STAMP(rec, 4);
-    // the thread's entry column's pivot mask
-    const int cpv = (tcol < g.ncols) ? s_cp[tcol] : 1;
     // chains as triangular solves; each factor sees the same operations in
-    // the same order as the written recursion, so both forms give the same
-    // bits.  Up to rank 16 a lane group per row (column) with row broadcasts;
-    // above, one thread per row (column) runs the factors in ascending z and
-    // reads the finished lower ones back from LDS (a lane group would need
-    // too many passes over the tile).
+    // the same order as the written recursion, so every form gives the same
+    // bits: a lane group per row (column) with row broadcasts for sixteen
+    // factors at a time, and matrix instructions to take the factors of
+    // earlier sixteens out
     const int nrw = rows_old ? 0 : g.nrows, ncw = cols_old ? 0 : g.ncols;
     // the Hilbert kernels only: the generic FP64 kernel has no registers to
     // spare for the reciprocals, and the generic FP32 one (batches) measured
     // slower with them
     constexpr bool RECIP = FNS == TT_FN_HILBERT;
     if (rk <= 8) {
-        solves_lg<V, 8, RECIP>(E, ld, g, Wt, Ut, Gr, Gc, s_piv, s_rpiv, s_rho, s_gam, TRm, TCm, rk, nrw, ncw, s_rp,
+        solves_lg<V, 8, RECIP>(E, ld, g, Wt, Ut, Gr, Gc, s_piv, s_rpiv, s_rho, s_gam, TRm, TCm, 0, rk, nrw, ncw, s_rp,
                                s_cp);
-    } else if (rk <= 16) {
-        solves_lg<V, 16, RECIP>(E, ld, g, Wt, Ut, Gr, Gc, s_piv, s_rpiv, s_rho, s_gam, TRm, TCm, rk, nrw, ncw, s_rp,
-                                s_cp);
     } else {
-        for (int e = tid; e < nrw + ncw; e += NT) {
-            if (e < nrw) {
-                const int ii = e;
-                for (int z = 1; z < rk; ++z) {
-                    V w = Wt[z * TRm + ii];
-#pragma unroll 8
-                    for (int zp = 0; zp < z; ++zp) w = vfma<V>(-Wt[zp * TRm + ii], Gr[tri(zp, z)], w);
-                    Wt[z * TRm + ii] = w;
-                }
-                if (!s_rp[ii])
-                    for (int z = 0; z < rk; ++z) {
-                        const int gz = s_gam[z];
-                        if (gz >= g.col0 && gz < g.col0 + g.ncols)
-                            E[(int64_t)(g.row0 + ii) * ld + gz] = Wt[z * TRm + ii];
-                    }
-            } else {
-                const int jj = e - nrw;
-                for (int z = 0; z < rk; ++z) {
-                    V u = Ut[z * TCm + jj];
-                    // Ut of a lower z already holds its finished factor over its pivot
-#pragma unroll 8
-                    for (int zp = 0; zp < z; ++zp) u = vfma<V>(-Gc[tri(zp, z)], Ut[zp * TCm + jj], u);
-                    const int rz = s_rho[z];
-                    if (!s_cp[jj] && rz >= g.row0 && rz < g.row0 + g.nrows) E[(int64_t)rz * ld + g.col0 + jj] = u;
-                    Ut[z * TCm + jj] = u / s_piv[z];
-                }
-            }
+        solves_lg<V, 16, RECIP>(E, ld, g, Wt, Ut, Gr, Gc, s_piv, s_rpiv, s_rho, s_gam, TRm, TCm, 0, rk, nrw, ncw, s_rp,
+                                s_cp);
+        for (int zb = 16; !LOW && zb < rk; zb += 16) {
+            lds_barrier();
+            solves_below<V>(Wt, Ut, Gr, Gc, TRm, TCm, zb, rk, nrw, ncw);
+            lds_barrier();
+            solves_lg<V, 16, RECIP>(E, ld, g, Wt, Ut, Gr, Gc, s_piv, s_rpiv, s_rho, s_gam, TRm, TCm, zb, rk, nrw, ncw,
+                                    s_rp, s_cp);
         }
     }
     lds_barrier();
     TT_STAMP(rec, 5);
-    if (tcol < g.ncols && !cpv) {
-        const int col = g.col0 + tcol;
-        const int ik1v = g.ik10 + tcol;
-        const bool hilbert = (FNS ? FNS : P->F.id) == TT_FN_HILBERT;
-        long long hsum = ik1v + 1;                 // integer index sum, exact in any order
-        for (int j = 0; j < npre; ++j) hsum += pre[j] + 1;
-        for (int j = 0; j < nsuf; ++j) hsum += suf[j] + 1;
-        // IL rows of the thread's column at once: each entry still takes
-        // every pivot out in insertion order, but the IL chains interleave
-        // and share each U(z, col) read
-        constexpr int IL = 4;
-        for (int ii0 = tr; ii0 < g.nrows; ii0 += IL * rpp) {
-            V x[IL];
-            int iv[IL];
-            bool ok[IL];
+    // entries in 16 x 16 blocks, a wavefront each: a lane evaluates four
+    // entries of one column, and the matrix cores take every pivot out of
+    // them in insertion order
+    const bool hilbert = (FNS ? FNS : P->F.id) == TT_FN_HILBERT;
+    long long hbase = 2;                       // integer index sum, exact in any order
+    for (int j = 0; j < npre; ++j) hbase += pre[j] + 1;
+    for (int j = 0; j < nsuf; ++j) hbase += suf[j] + 1;
+    const int lane = tid & 63, lr = lane & 15, lq = lane >> 4, nbc = (g.ncols + 15) >> 4;
+    const int nblk = ((g.nrows + 15) >> 4) * nbc;
+    for (int b = __builtin_amdgcn_readfirstlane(tid >> 6); b < nblk; b += NT / 64) {
+        const int br = b / nbc, r0 = 16 * br, c0 = 16 * (b - br * nbc);
+        const int jj = min(c0 + lr, g.ncols - 1), ik1v = g.ik10 + jj;
+        const bool colok = c0 + lr < g.ncols && !s_cp[jj];
+        typename Mfma<V>::vec x;
+        int iv[4];
 #pragma unroll
-            for (int j = 0; j < IL; ++j) {
-                const int ii = ii0 + j * rpp;
-                iv[j] = min(ii, g.nrows - 1);
-                ok[j] = ii < g.nrows && !s_rp[iv[j]];
-                const int ikv = g.ik0 + iv[j];
-                if (hilbert) {
-                    x[j] = (V)1 / ((V)(hsum + ikv + 1) + (V)P->F.shift);
-                } else {
-                    x[j] = fn_value_ix<V, FNS>(P->F, [&](int jj) {
-                        return jj < npre ? pre[jj] : (jj == k - 1 ? ikv : (jj == k ? ik1v : suf[jj - k - 1]));
-                    });
-                }
+        for (int r = 0; r < 4; ++r) {
+            iv[r] = min(r0 + Mfma<V>::row(lq, r), g.nrows - 1);
+            const int ikv = g.ik0 + iv[r];
+            if (hilbert) {
+                x[r] = (V)1 / ((V)(hbase + ikv + ik1v) + (V)P->F.shift);
+            } else {
+                x[r] = fn_value_ix<V, FNS>(P->F, [&](int j) {
+                    return j < npre ? pre[j] : (j == k - 1 ? ikv : (j == k ? ik1v : suf[j - k - 1]));
+                });
             }
-            for (int z = 0; z < rk; ++z) {
-                const V uz = Ut[z * TCm + tcol];
+        }
+        x = eliminate<V>(x, Wt + min(r0 + lr, g.nrows - 1), TRm, Ut + jj, TCm, rk, lq);
+        if (colok) {
+            const int col = g.col0 + jj;
 #pragma unroll
-                for (int j = 0; j < IL; ++j) x[j] = vfma<V>(-Wt[z * TRm + iv[j]], uz, x[j]);
-            }
-#pragma unroll
-            for (int j = 0; j < IL; ++j) {
-                if (!ok[j]) continue;
-                const int row = g.row0 + iv[j];
-                E[(int64_t)row * ld + col] = x[j];
-                const double ax = (double)fabs(x[j]);
+            for (int r = 0; r < 4; ++r) {
+                if (r0 + Mfma<V>::row(lq, r) >= g.nrows || s_rp[iv[r]]) continue;
+                const int row = g.row0 + iv[r];
+                E[(int64_t)row * ld + col] = x[r];
+                const double ax = (double)fabs(x[r]);
                 const uint64_t key = ((uint64_t)row << 32) | (uint32_t)col;
-                if (better(ax, key, bv, bk)) { bv = ax; bk = key; bs = (double)x[j]; }
+                if (better(ax, key, bv, bk)) { bv = ax; bk = key; bs = (double)x[r]; }
             }
         }
     }
@@ -744,7 +812,7 @@ __device__ void new_tile(const ProbDev *__restrict__ P, const KTile &K, int u, i
 
 // Fixed grid striding over work units: first the new-entry tiles (one per
 // workgroup), then the stored tiles four at a time (one per wavefront).
-template <typename V, int FNS>
+template <typename V, int FNS, bool LOW>
 __device__ void sweep_body(const ProbDev *__restrict__ P, const ProbState *S, int nk, int blk, int nblk,
                            int sweep = -1)
 {
@@ -763,8 +831,12 @@ __device__ void sweep_body(const ProbDev *__restrict__ P, const ProbState *S, in
     // previous commit left (read before the flag is known, so that all of
     // them are in flight together)
     const int stop = as_global(&S->stop)[0];
-    if (tid < nk) load_words(ks[tid], &S->ks[tid]);
-    if (tid < SHAPE_WORDS) ((int *)&sh)[tid] = as_global((const int *)&S->sh)[tid];
+    constexpr int KSW = (int)(sizeof(KSweep) / 4);
+    for (int w = tid; w < nk * KSW + SHAPE_WORDS; w += NT) {
+        const bool isk = w < nk * KSW;
+        const int x = isk ? as_global((const int *)S->ks)[w] : as_global((const int *)&S->sh)[w - nk * KSW];
+        *(isk ? (int *)ks + w : (int *)&sh + (w - nk * KSW)) = x;
+    }
     if (stop) return;                   // the same value in every thread
     __syncthreads();
     TT_STAMP(rec, 1);
@@ -796,7 +868,7 @@ __device__ void sweep_body(const ProbDev *__restrict__ P, const ProbState *S, in
             R = __builtin_amdgcn_readfirstlane(R);
             C = __builtin_amdgcn_readfirstlane(C);
             const KTile &K = P->kt[u];
-            new_tile<V, FNS>(P, K, u, R, C, ks[u], bv, bk, bs, (V *)smem_raw, nrec);
+            new_tile<V, FNS, LOW>(P, K, u, R, C, ks[u], bv, bk, bs, (V *)smem_raw, nrec);
             TT_STAMP_ADD(rec, 10, 1);
             if (tid == 0) {
                 const gptr_t<Cand> c = as_global(K.cand) + idx;
@@ -810,21 +882,23 @@ __device__ void sweep_body(const ProbDev *__restrict__ P, const ProbState *S, in
             if (st < nst) {
                 int u = 0;
                 while (u + 1 < nk && st >= sh.soff[u + 1]) ++u;
-                const int idx = st - sh.soff[u], CTs = sh.CTs[u];
+                const int idx = st - sh.soff[u], CTs = sh.CTs[u], lsp = __builtin_amdgcn_readfirstlane(sh.lsp[u]);
+                const int tile = idx >> lsp;
                 // the tile is the wavefront's (values read from LDS are
                 // per-lane to the compiler): uniform geometry and loop counts
                 u = __builtin_amdgcn_readfirstlane(u);
-                const int R = __builtin_amdgcn_readfirstlane(idx / CTs);
-                const int C = __builtin_amdgcn_readfirstlane(idx - R * CTs);
+                const int R = __builtin_amdgcn_readfirstlane(tile / CTs);
+                const int C = __builtin_amdgcn_readfirstlane(tile - R * CTs);
+                const int part = __builtin_amdgcn_readfirstlane(idx - (tile << lsp));
                 const KTile &K = P->kt[u];
-                const TileGeom g = tile_geom(K, u, R, C);
+                const TileGeom g = tile_geom(K, u, R, C, part, lsp);
 #ifdef TT_STAMPS
                 // wave 0's first stored tile: geometry known, tile done
                 const bool first_st = rec && wid == 0 && rec[11] == 0;
                 if (first_st && lane == 0) rec[7] = __builtin_amdgcn_s_memrealtime();
 #endif
                 // 8 rows per batch of loads: more would cost occupancy
-                stored_tile_wave<V, 8>(K, ks[u], g, bv, bk, bs);
+                if (g.nrows > 0) stored_tile_wave<V, 8>(K, ks[u], g, bv, bk, bs);
                 wave_best(bv, bk, bs);
                 if (lane == 0) {
                     const gptr_t<Cand> c = as_global(K.cand) + (sh.noff[u + 1] - sh.noff[u] + idx);
@@ -843,10 +917,10 @@ __device__ void sweep_body(const ProbDev *__restrict__ P, const ProbState *S, in
 #endif
 }
 
-template <typename V, int FNS = 0>
+template <typename V, int FNS, bool LOW>
 static __global__ void __launch_bounds__(NT, 4) k_sweep(const ProbDev *__restrict__ P, SweepArgs a)
 {
-    sweep_body<V, FNS>(P, a.S, a.nk, blockIdx.x, gridDim.x, a.sweep);
+    sweep_body<V, FNS, LOW>(P, a.S, a.nk, blockIdx.x, gridDim.x, a.sweep);
 }
 
 // ---------------------------------------------------------------------------
@@ -912,8 +986,7 @@ struct CommitIn {
     int err;                         // the state's error code, kept current here
     double tau;
     unsigned long long acc[3];       // alg_bytes, new_entries, pivoted
-    int off[2][TT_MAX_D + 1];        // the sweep's tile offsets (new, stored)
-    Cand prev[TT_MAX_D];             // best candidates of the sweep before
+    int ntl[TT_MAX_D];               // candidates of the sweep
     KDev kd[TT_MAX_D];
     // the problem's fields the commit reads later, read up front
     int rook, r_max, fp32, rcap, hist_cap;
@@ -992,11 +1065,11 @@ __device__ void commit_body(const ProbDev *__restrict__ P, ProbState *S, int swe
             }
         }
     }
-    if (tid < nk) {
-        load_words(ci.ks[tid], &S->ks[tid]);
-        load_words(ci.prev[tid], &S->prev[tid]);
-    }
-    if (tid >= 64 && tid < 64 + 2 * (TT_MAX_D + 1)) ci.off[0][tid - 64] = as_global(&S->sh.noff[0])[tid - 64];
+    // (a word per thread: a struct per thread is as many loads in a row)
+    constexpr int KSW = (int)(sizeof(KSweep) / 4);
+    static_assert(TT_MAX_D * KSW <= NTC, "one word of the shapes per thread");
+    if (tid < nk * KSW) ((int *)ci.ks)[tid] = as_global((const int *)S->ks)[tid];
+    if (tid >= 64 && tid < 64 + nk) ci.ntl[tid - 64] = as_global(S->sh.ntl)[tid - 64];
     if (tid <= d) ci.rold[tid] = as_global(&S->r[par][tid])[0];
     if (tid == NTC - 1) {
         ci.stop = as_global(&S->stop)[0];
@@ -1026,13 +1099,14 @@ __device__ void commit_body(const ProbDev *__restrict__ P, ProbState *S, int swe
     __shared__ unsigned long long s_rcnt[TT_MAX_D];
     __shared__ int s_prop[TT_MAX_D], s_rnew[TT_MAX_D + 1];
     __shared__ unsigned long long s_bytes[TT_MAX_D], s_new[TT_MAX_D], s_piv[TT_MAX_D];
-    __shared__ int s_geo[TT_MAX_D][4];
+    __shared__ int s_geo[TT_MAX_D][6];
+    __shared__ Cand s_best[TT_MAX_D];
 
     // best candidate of unfolding us over this wavefront's share of the
     // tiles, in every lane
     auto scan = [&](int us, double &bv, uint64_t &bk, double &bs) {
         const KDev &K = kd[us];
-        const int ntl = rook ? K.nrb * K.ncb : ci.off[0][us + 1] - ci.off[0][us] + ci.off[1][us + 1] - ci.off[1][us];
+        const int ntl = rook ? K.nrb * K.ncb : ci.ntl[us];
         bv = -1.0; bs = 0.0; bk = ~0ULL;
         if (rook && sl == 0) {
             // residuals the block searches looked at
@@ -1051,11 +1125,6 @@ __device__ void commit_body(const ProbDev *__restrict__ P, ProbState *S, int swe
             i0 += 64 * wpu * CB;
         }
         scan_cands(as_global((const Cand *)K.cand), i0, ntl, wpu, bv, bk, bs);
-        // stored entries that no pivot changed: their best is the last sweep's
-        if (!rook && sl == 0 && lane == 0 && !ks[us].apply &&
-            better(ci.prev[us].v, ci.prev[us].key, bv, bk)) {
-            bv = ci.prev[us].v; bk = ci.prev[us].key; bs = ci.prev[us].sv;
-        }
         wave_best(bv, bk, bs);
     };
 
@@ -1103,9 +1172,9 @@ __device__ void commit_body(const ProbDev *__restrict__ P, ProbState *S, int swe
         if (lane == 0) {
             if (sweep < ci.hist_cap) as_global((double *)K.hist)[sweep] = e;
             S->last_best[u] = e;
-            S->prev[u].v = bv;
-            S->prev[u].key = bk;
-            S->prev[u].sv = bs;
+            s_best[u].v = bv;
+            s_best[u].key = bk;
+            s_best[u].sv = bs;
             if (over && !propose) S->capped = 1;
             if (propose && bs == 0.0) {
                 S->err = TT_ESINGULAR;
@@ -1140,6 +1209,8 @@ __device__ void commit_body(const ProbDev *__restrict__ P, ProbState *S, int swe
             s_geo[u][1] = K.nk1;
             s_geo[u][2] = K.RTp;
             s_geo[u][3] = K.CTq;
+            s_geo[u][4] = K.RTn;
+            s_geo[u][5] = K.smax;
         }
     };
 
@@ -1189,7 +1260,8 @@ __device__ void commit_body(const ProbDev *__restrict__ P, ProbState *S, int swe
         int nn = 0, ns = 0;
         if (u < nk) {
             const int k = u + 1;
-            const int knk = s_geo[u][0], knk1 = s_geo[u][1], kRTp = s_geo[u][2], kCTq = s_geo[u][3];
+            const int knk = s_geo[u][0], knk1 = s_geo[u][1], kRTp = s_geo[u][2], kCTq = s_geo[u][3],
+                      kRTn = s_geo[u][4];
             KSweep n;
             n.rk = s_rnew[k];
             n.apply = s_prop[u];
@@ -1203,14 +1275,23 @@ __device__ void commit_body(const ProbDev *__restrict__ P, ProbState *S, int swe
             S->ks[u] = n;
             S->r[par ^ 1][k] = s_rnew[k];
             // tile counts from the ranks (rows r_{k-1} n_k, columns n_{k+1} r_{k+1})
-            const int RT = s_rnew[k - 1] * kRTp, CT = s_rnew[k + 1] * kCTq;
-            const int RTs = s_rold[k - 1] * kRTp, CTs = s_rold[k + 1] * kCTq;
+            const int RT = s_rnew[k - 1] * kRTn, CT = s_rnew[k + 1] * kCTq;
+            const int RTs = s_rold[k - 1] * kRTn, CTs = s_rold[k + 1] * kCTq;
             S->sh.RT[u] = RT;
             S->sh.CT[u] = CT;
             S->sh.RTs[u] = RTs;
             S->sh.CTs[u] = CTs;
             nn = RT * CT - RTs * CTs;
-            ns = s_prop[u] ? RTs * CTs : 0;    // unchanged stored entries are not visited
+            // unchanged stored entries are not visited
+            ns = s_prop[u] ? s_rold[k - 1] * kRTp * CTs : 0;
+            const int lsp = stored_split(ns, nk, s_geo[u][5]);
+            S->sh.lsp[u] = lsp;
+            ns <<= lsp;
+            S->sh.ntl[u] = nn + (s_prop[u] ? ns : 1);
+            if (!s_prop[u] && !rook) {
+                const gptr_t<Cand> c = as_global(kd[u].cand) + nn;
+                c->v = s_best[u].v; c->key = s_best[u].key; c->sv = s_best[u].sv;
+            }
         }
         // inclusive scans over the first 16 lanes (nk <= 15 carry counts)
         const int pn = row_scan_incl(nn), ps = row_scan_incl(ns);
@@ -1469,7 +1550,6 @@ __device__ void seeded_pivots(const ProbDev *__restrict__ P, ProbState *S, const
             ks.agam = 0;
             ks.apiv = 0.0;
             S->ks[u] = ks;
-            cand_none(S->prev[u]);           // nothing stored, nothing searched yet
             S->r[0][k] = m;
             S->r[1][k] = m;
             P->hm->r[k] = m;
@@ -1480,10 +1560,12 @@ __device__ void seeded_pivots(const ProbDev *__restrict__ P, ProbState *S, const
         for (int u = 0; u < nk; ++u) {
             const KDev &K = P->kd[u];
             const int mp = u >= 1 ? plan->m[u - 1] : 1, mn = u + 1 < nk ? plan->m[u + 1] : 1;
-            S->sh.RT[u] = mp * K.RTp;
+            S->sh.RT[u] = mp * K.RTn;
             S->sh.CT[u] = mn * K.CTq;
             S->sh.RTs[u] = 0;
             S->sh.CTs[u] = 0;
+            S->sh.lsp[u] = 0;
+            S->sh.ntl[u] = S->sh.RT[u] * S->sh.CT[u];
             S->sh.noff[u] = no;
             S->sh.soff[u] = 0;
             no += S->sh.RT[u] * S->sh.CT[u];
@@ -2989,12 +3071,12 @@ static __global__ void __launch_bounds__(NT) k_init_eval_b(const ProbDev *__rest
     init_eval_body<V, 0>(P, blockIdx.y, blockIdx.x, gridDim.x);
 }
 
-template <typename V>
+template <typename V, bool LOW>
 static __global__ void __launch_bounds__(NT, 4) k_sweep_b(const ProbDev *__restrict__ Pa, BatchMap bm)
 {
     const int i = batch_find(bm, blockIdx.x);
     const ProbDev *P = Pa + bm.p[i];
-    sweep_body<V, 0>(P, P->S, P->nk, blockIdx.x - bm.boff[i], bm.boff[i + 1] - bm.boff[i]);
+    sweep_body<V, 0, LOW>(P, P->S, P->nk, blockIdx.x - bm.boff[i], bm.boff[i + 1] - bm.boff[i]);
 }
 
 template <typename V>
