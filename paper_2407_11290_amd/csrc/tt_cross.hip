@@ -313,17 +313,18 @@ int Problem::allocate()
         int dev = 0;
         HIPCHK(hipGetDevice(&dev));
         HIPCHK(hipDeviceGetAttribute(&lds_limit, hipDeviceAttributeMaxSharedMemoryPerBlock, dev));
-        // the search kernel's static LDS (shapes, commit scratch) comes off the top
-        // (the larger of the Hilbert kernel's and the general one's)
-        hipFuncAttributes fa, fh;
-        if (fp32) {
-            HIPCHK(hipFuncGetAttributes(&fa, reinterpret_cast<const void *>(&k_sweep<float, 0, false>)));
-            HIPCHK(hipFuncGetAttributes(&fh, reinterpret_cast<const void *>(&k_sweep<float, TT_FN_HILBERT, false>)));
-        } else {
-            HIPCHK(hipFuncGetAttributes(&fa, reinterpret_cast<const void *>(&k_sweep<double, 0, false>)));
-            HIPCHK(hipFuncGetAttributes(&fh, reinterpret_cast<const void *>(&k_sweep<double, TT_FN_HILBERT, false>)));
+        // the search kernels' static LDS comes off the top: a fixed reserve, so
+        // that the shapes that fit do not depend on a kernel's build (the
+        // kinetic kernel, which has more, is used where it fits too)
+        lds_static = fp32 ? 3824 : 4336;
+        lds_kin = 0;
+        if (fn.dev.id == TT_FN_MAXWELL_2D2V || fn.dev.id == TT_FN_MAXWELL_3D3V) {
+            hipFuncAttributes fa;
+            HIPCHK(hipFuncGetAttributes(
+                &fa, fp32 ? reinterpret_cast<const void *>(&k_sweep<float, TT_FN_MAXWELL_3D3V, false>)
+                          : reinterpret_cast<const void *>(&k_sweep<double, TT_FN_MAXWELL_3D3V, false>)));
+            lds_kin = (int)fa.sharedSizeBytes;
         }
-        lds_static = (int)std::max(fa.sharedSizeBytes, fh.sharedSizeBytes);
     }
     const size_t w = fp32 ? 4 : 8;
     ProbDev &H = hP;
@@ -686,9 +687,13 @@ template <typename V> int Problem::launch_ahead()
         for (int k = 0; k <= d; ++k) rst[k] = rub[k];
         // the Hilbert tensor gets a kernel built for it alone (fewer
         // registers, more workgroups resident); the others share one
-        // and ranks up to 16 one without the code for more
-        auto kern = low ? (hil ? k_sweep<V, TT_FN_HILBERT, true> : k_sweep<V, 0, true>)
-                        : (hil ? k_sweep<V, TT_FN_HILBERT, false> : k_sweep<V, 0, false>);
+        // and ranks up to 16 one without the code for more; the kinetic
+        // tensors' entries split into parts of a tile (KinTile)
+        const bool kin = lds_kin > 0 && lds + lds_kin <= (size_t)lds_limit;
+        auto kern = low ? (hil ? k_sweep<V, TT_FN_HILBERT, true>
+                               : kin ? k_sweep<V, TT_FN_MAXWELL_3D3V, true> : k_sweep<V, 0, true>)
+                        : (hil ? k_sweep<V, TT_FN_HILBERT, false>
+                               : kin ? k_sweep<V, TT_FN_MAXWELL_3D3V, false> : k_sweep<V, 0, false>);
         if (rook) {
             // factors: one thread per superblock row and column (bounded by
             // the ranks this sweep can have), then one workgroup per block

