@@ -1972,42 +1972,6 @@ struct RookGeom {
     int np, nq, lo, len, lo1, len1;
 };
 
-// Filled by one thread into workgroup-shared pref, suf and g.
-__device__ inline void rook_block_geom(const ProbDev *__restrict__ P, int u, int b, const KSweep &ks, int *pref,
-                                       int *suf, RookGeom &g)
-{
-    const KDev &K = P->kd[u];
-    const int k = u + 1, d = P->d;
-    const int rb = b % K.nrb, cb = b / K.nrb;
-    int c[TT_MAX_D];
-    int x = rb;
-    for (int j = 0; j < k; ++j) { c[j] = x % P->grid[j]; x /= P->grid[j]; }
-    x = cb;
-    for (int j = k; j < d; ++j) { c[j] = x % P->grid[j]; x /= P->grid[j]; }
-    const int rp = ks.nr / K.nk, rq = ks.nc / K.nk1;
-    int np = 0;
-    for (int p = 0; p < rp; ++p) {
-        bool ok = true;
-        for (int j = 0; j < k - 1 && ok; ++j)
-            ok = grid_piece(as_global((const int *)P->kd[u - 1].Ifull)[p * (k - 1) + j], P->F.n[j], P->grid[j]) == c[j];
-        if (ok) pref[np++] = p;
-    }
-    int nq = 0;
-    for (int q = 0; q < rq; ++q) {
-        bool ok = true;
-        for (int j = 0; j < d - k - 1 && ok; ++j)
-            ok = grid_piece(as_global((const int *)P->kd[u + 1].Jfull)[q * (d - k - 1) + j], P->F.n[k + 1 + j], P->grid[k + 1 + j]) ==
-                 c[k + 1 + j];
-        if (ok) suf[nq++] = q;
-    }
-    g.np = np;
-    g.nq = nq;
-    g.lo = piece_start(c[k - 1], K.nk, P->grid[k - 1]);
-    g.len = piece_start(c[k - 1] + 1, K.nk, P->grid[k - 1]) - g.lo;
-    g.lo1 = piece_start(c[k], K.nk1, P->grid[k]);
-    g.len1 = piece_start(c[k] + 1, K.nk1, P->grid[k]) - g.lo1;
-}
-
 // One subtensor block of superblock u in this sweep, staged in LDS: its
 // prefixes and suffixes with their index tuples, and the positions of the
 // unfolding's pivots.  An entry at a position of the block then needs no
@@ -2055,16 +2019,48 @@ struct RookBlock {
     }
 };
 
-// Thread 0 reads the sweep's shapes and finds the block's geometry, then
-// every thread stages the tuples and the pivot positions.  Ends with a
-// barrier.
+// The block's geometry (the first wavefront tests a prefix per lane, the
+// second a suffix: one after the other in one thread they took up to 10 us of
+// dependent reads), then every thread stages the tuples and the pivot
+// positions.  Ends with a barrier.
 __device__ inline void rook_block_load(const ProbDev *__restrict__ P, int u, int b, RookBlock &B)
 {
     const KDev &K = P->kd[u];
-    const int k = u + 1, npre = k - 1, nsuf = P->d - k - 1;
-    if (threadIdx.x == 0) {
+    const int k = u + 1, d = P->d, npre = k - 1, nsuf = d - k - 1;
+    const int wid = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    static_assert(TT_MAX_RANK <= 64 && NT >= 192, "one prefix (suffix) per lane of a wavefront, one more for the rest");
+    if (wid < 2) {
+        // block digits of the tuples' modes against the block's
+        const bool pre = wid == 0;
+        const int nt = pre ? P->S->ks[u].nr / K.nk : P->S->ks[u].nc / K.nk1, len = pre ? npre : nsuf;
+        const int j0 = pre ? 0 : k + 1;
+        const gptr_t<const int> tup = as_global((const int *)(len == 0 ? nullptr : pre ? P->kd[u - 1].Ifull : P->kd[u + 1].Jfull));
+        int x = pre ? b % K.nrb : (b / K.nrb) / P->grid[k];
+        bool ok = lane < nt;
+        for (int j = 0; j < len; ++j) {
+            const int C = P->grid[j0 + j], c = x % C;
+            x /= C;
+            if (ok) ok = grid_piece(tup[lane * len + j], P->F.n[j0 + j], C) == c;
+        }
+        const unsigned long long m = __ballot(ok);
+        if (ok) (pre ? B.pref : B.suf)[__popcll(m & ((1ull << lane) - 1))] = lane;
+        if (lane == 0) {
+            // the piece of mode k (k + 1)
+            const int C = P->grid[pre ? k - 1 : k], n = pre ? K.nk : K.nk1;
+            const int c = pre ? x % C : (b / K.nrb) % C;
+            const int lo = piece_start(c, n, C), ln = piece_start(c + 1, n, C) - lo;
+            if (pre) {
+                B.g.np = __popcll(m);
+                B.g.lo = lo;
+                B.g.len = ln;
+            } else {
+                B.g.nq = __popcll(m);
+                B.g.lo1 = lo;
+                B.g.len1 = ln;
+            }
+        }
+    } else if (threadIdx.x == 128) {
         B.ks = P->S->ks[u];
-        rook_block_geom(P, u, b, B.ks, B.pref, B.suf, B.g);
         B.nk = K.nk;
         B.nk1 = K.nk1;
         B.npre = npre;
@@ -2364,6 +2360,15 @@ __device__ void rook_wstep_body(const ProbDev *__restrict__ P, int nk, int p, in
     if (!rook_wg_of(P, nk, G, wg, u, b, g)) return;
     const KDev &K = P->kd[u];
     const int nb = K.nrb * K.ncb;
+    // a block that was done before the last phase stays as it is (its partial
+    // bests are not read again): nothing to load but its state
+    if (p > 1) {
+        const RookState &old = K.rst[(int64_t)((p - 1) & 1) * nb + b];
+        if (!old.active) {                      // the same value in every thread
+            if (g == 0 && tid == 0) K.rst[(int64_t)(p & 1) * nb + b] = old;
+            return;
+        }
+    }
     __shared__ RookBlock B;
     __shared__ RookState st;
     __shared__ double s_f[TT_MAX_RANK];
