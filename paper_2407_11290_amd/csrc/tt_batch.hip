@@ -114,6 +114,16 @@ int Engine::admit(Problem *Q, void *user)
     Q->escalated = Q->force_fp64 ? 1 : 0;
     ProbDev &D = hPa[i];
     D = Q->hP;
+    // in a batch the chip is full: stored tiles are searched whole
+    for (int u = 0, acc = 0; u < Q->d - 1; ++u) {
+        KDev &K = D.kd[u];
+        K.smax = 0;
+        D.sh0.lsp[u] = 0;
+        D.sh0.soff[u] = acc;
+        D.sh0.ntl[u] = K.RTp * K.CTq;
+        acc += D.sh0.ntl[u];
+        D.sh0.soff[u + 1] = acc;
+    }
     D.S = dS + i;
     D.hm = dhm + i;
     D.run.seed = Q->opt.seed;
@@ -211,7 +221,7 @@ template <typename V> int Engine::launch_sweep(std::vector<int> &ids)
             int tot = 0;
             for (int u = 0; u < d - 1; ++u) {
                 const int k = u + 1;
-                const KDev &K = Q.hP.kd[u];
+                const KDev &K = hPa[s.idx].kd[u];
                 int nnew, nst;
                 low = low && s.rub[k] <= 16;
                 sweep_units(K, s.rub, s.rst, k, d - 1, nnew, nst);
@@ -505,12 +515,21 @@ extern "C" int tt_batch_run(tt_cross_h *hs, int count, void *hip_stream)
         Q.restart_cause = 0;
         if (Q.dev_plan_npts != 0) {
             HIPCHK(hipMemcpyAsync(&Q.d_plan->npts, &zero, sizeof(int), hipMemcpyHostToDevice, Q.stream));
+            HIPCHK(hipStreamSynchronize(Q.stream));
             Q.dev_plan_npts = 0;
         }
     }
     hipStream_t stream = hip_stream ? (hipStream_t)hip_stream : hs[0]->p.stream;
     // the handles' own streams must not still be working on these buffers
-    for (int i = 0; i < count; ++i) HIPCHK(hipStreamSynchronize(hs[i]->p.stream));
+    // a handle's own stream carries its calls alone, which have ended (waiting
+    // for 512 of them cost up to 5 ms); a caller's stream may carry more
+    hipStream_t seen = nullptr;
+    for (int i = 0; i < count; ++i) {
+        const Problem &Q = hs[i]->p;
+        if (Q.own_stream || Q.stream == seen) continue;
+        seen = Q.stream;
+        HIPCHK(hipStreamSynchronize(seen));
+    }
     // one engine per thread, kept for later batches (never torn down, so that
     // nothing is freed after the runtime has shut down at process exit)
     static thread_local Engine *engp = nullptr;

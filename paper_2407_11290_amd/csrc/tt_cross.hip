@@ -254,11 +254,11 @@ void Problem::release()
 {
     for (void *p : allocs) (void)hipFree(p);
     allocs.clear();
+    slab_left = 0;
     for (hipEvent_t e : prof_events) (void)hipEventDestroy(e);
     prof_events.clear();
     if (hm) { (void)hipHostFree(hm); hm = nullptr; }
-    if (hS_pinned) { (void)hipHostFree(hS_pinned); hS_pinned = nullptr; }
-    if (h_part) { (void)hipHostFree(h_part); h_part = nullptr; }
+    if (h_out) { (void)hipHostFree(h_out); h_out = nullptr; hS_pinned = nullptr; h_part = nullptr; }
     for (hipEvent_t &e : run_ev)
         if (e) { (void)hipEventDestroy(e); e = nullptr; }
     fn.free_device();
@@ -273,6 +273,27 @@ int Problem::dalloc(void **p, size_t bytes)
 {
     *p = nullptr;
     if (bytes == 0) bytes = 16;
+    // small buffers (a dozen per unfolding) come from slabs: each allocation
+    // of its own takes some 5 us of a new handle's first run
+    constexpr size_t SMALL = (size_t)32 << 10, SLAB = (size_t)256 << 10;
+    if (bytes <= SMALL) {
+        bytes = (bytes + 255) & ~(size_t)255;
+        if (slab_left < bytes) {
+            void *s = nullptr;
+            const hipError_t es = hipMalloc(&s, SLAB);
+            if (es != hipSuccess) {
+                (void)hipGetLastError();
+                return set_err(TT_ENOMEM, "hipMalloc(%zu) failed: %s", SLAB, hipGetErrorString(es));
+            }
+            allocs.push_back(s);
+            slab = (char *)s;
+            slab_left = SLAB;
+        }
+        *p = slab;
+        slab += bytes;
+        slab_left -= bytes;
+        return TT_OK;
+    }
     hipError_t e = hipMalloc(p, bytes);
     if (e != hipSuccess) {
         *p = nullptr;
@@ -499,7 +520,6 @@ int Problem::allocate()
     if ((st = dalloc((void **)&d_ctab, sizeof(double) * CT_STRIDE * (d - 1))) != TT_OK) return st;
     if ((st = dalloc((void **)&d_vals, sizeof(double) * opt.n_samples)) != TT_OK) return st;
     if ((st = dalloc((void **)&d_spart, sizeof(SamplePart) * sample_blocks(opt.n_samples))) != TT_OK) return st;
-    if ((st = dalloc((void **)&d_part, sizeof(double) * 2 * NBV)) != TT_OK) return st;
     if ((st = dalloc((void **)&d_plan, sizeof(SeedPlan))) != TT_OK) return st;
     HIPCHK(hipMemset(d_plan, 0, sizeof(SeedPlan)));
     dev_plan_npts = 0;
@@ -594,11 +614,21 @@ template <typename V> int Problem::begin_sweeps()
     if (!run_ev[0]) HIPCHK(hipEventCreate(&run_ev[0]));
     if (!run_ev[1]) HIPCHK(hipEventCreate(&run_ev[1]));
     if (!run_ev[2]) HIPCHK(hipEventCreateWithFlags(&run_ev[2], hipEventDisableTiming));
-    if (!hS_pinned) HIPCHK(hipHostMalloc((void **)&hS_pinned, sizeof(ProbState), hipHostMallocDefault));
-    if (!h_part) HIPCHK(hipHostMalloc((void **)&h_part, sizeof(double) * 2 * NBV, hipHostMallocDefault));
+    // written by the kernels themselves: the final state, the check's sums
+    if (!h_out) {
+        constexpr size_t off = (sizeof(ProbState) + 255) & ~(size_t)255;
+        void *dev = nullptr;
+        HIPCHK(hipHostMalloc(&h_out, off + sizeof(double) * 2 * NBV, hipHostMallocMapped | hipHostMallocCoherent));
+        HIPCHK(hipHostGetDevicePointer(&dev, h_out, 0));
+        hS_pinned = (ProbState *)h_out;
+        h_part = (double *)((char *)h_out + off);
+        d_hS = (ProbState *)dev;
+        d_hpart = (double *)((char *)dev + off);
+    }
     hm->sweeps_done = 0;
     hm->stop = 0;
     hm->err = 0;
+    hm->singular = 0;
     std::atomic_thread_fence(std::memory_order_seq_cst);
 #ifdef TT_STAMPS
     HIPCHK(hipMemsetAsync(hP.stamps, 0, sizeof(unsigned long long) * stamp_words, stream));
@@ -817,49 +847,66 @@ template <typename V> int Problem::launch_tail()
         else k_core_piv<0><<<d - 1, A4W, lp, stream>>>(dP, ca, d_ctab);
         HIPCHK(hipGetLastError());
         if (maxr <= 32) {
-            if (hil) k_cores_t<TT_FN_HILBERT, 32><<<blocks, A4W, lt, stream>>>(dP, ca, d_cores, d_ctab);
-            else k_cores_t<0, 32><<<blocks, A4W, lt, stream>>>(dP, ca, d_cores, d_ctab);
+            if (hil) k_cores_t<TT_FN_HILBERT, 32><<<blocks + 1, A4W, lt, stream>>>(dP, ca, d_cores, d_ctab, d_hS);
+            else k_cores_t<0, 32><<<blocks + 1, A4W, lt, stream>>>(dP, ca, d_cores, d_ctab, d_hS);
         } else {
-            if (hil) k_cores_t<TT_FN_HILBERT, TT_MAX_RANK><<<blocks, A4W, lt, stream>>>(dP, ca, d_cores, d_ctab);
-            else k_cores_t<0, TT_MAX_RANK><<<blocks, A4W, lt, stream>>>(dP, ca, d_cores, d_ctab);
+            if (hil) k_cores_t<TT_FN_HILBERT, TT_MAX_RANK><<<blocks + 1, A4W, lt, stream>>>(dP, ca, d_cores, d_ctab, d_hS);
+            else k_cores_t<0, TT_MAX_RANK><<<blocks + 1, A4W, lt, stream>>>(dP, ca, d_cores, d_ctab, d_hS);
         }
     } else {
         const size_t lc = sizeof(double) * ((size_t)2 * maxr * (maxr + 1) + (size_t)2 * maxr * A4W);
-        if (hil) k_cores<TT_FN_HILBERT><<<blocks, A4W, lc, stream>>>(dP, ca, d_cores);
-        else k_cores<0><<<blocks, A4W, lc, stream>>>(dP, ca, d_cores);
+        if (hil) k_cores<TT_FN_HILBERT><<<blocks + 1, A4W, lc, stream>>>(dP, ca, d_cores, d_hS);
+        else k_cores<0><<<blocks + 1, A4W, lc, stream>>>(dP, ca, d_cores, d_hS);
     }
     HIPCHK(hipGetLastError());
     HIPCHK(hipEventRecord(run_ev[1], stream));
-    HIPCHK(hipMemcpyAsync(hS_pinned, hP.S, sizeof(ProbState), hipMemcpyDeviceToHost, stream));
-    HIPCHK(hipEventRecord(run_ev[2], stream));
+    const int64_t R = verify_samples();
+    if (R > 0) {
+        // a13: sampled relative error over an independent SplitMix64(seed + 1)
+        // set, queued behind the cores (its result is looked at after
+        // theirs); with restarts on, every sample's error as well
+        double *serr = nullptr;
+        if (restarts_on()) {
+            if (serr_cap < R) {
+                const int st = dalloc((void **)&d_serr, sizeof(double) * R);
+                if (st != TT_OK) return st;
+                serr_cap = R;
+            }
+            serr = d_serr;
+        }
+        k_verify<<<NBV, NT, 0, stream>>>(dP, d_cores, R, opt.seed + 1, d_hpart, serr);
+        HIPCHK(hipGetLastError());
+        HIPCHK(hipEventRecord(run_ev[2], stream));
+    }
     phase = PH_TAIL;
     return 1;
 }
 
-// Waits for (wait = true) or checks run_ev[2]: 1 done, 0 not yet, < 0 error.
-int Problem::tail_event(bool wait)
+// Waits for (wait = true) or checks event ev: 1 done, 0 not yet, < 0 error.
+int Problem::tail_event(hipEvent_t ev, bool wait)
 {
     if (wait) {
-        HIPCHK(hipEventSynchronize(run_ev[2]));
+        HIPCHK(hipEventSynchronize(ev));
         return 1;
     }
-    const hipError_t q = hipEventQuery(run_ev[2]);
+    const hipError_t q = hipEventQuery(ev);
     if (q == hipErrorNotReady) return 0;
     if (q != hipSuccess) return set_err(TT_EDEVICE, "run failed: %s", hipGetErrorString(q));
     return 1;
 }
 
-// Step 2 done: results from the final state; then step 3 is queued if the
-// run has a sampled-error check.
+// Step 2 done: results from the final state; then step 3 if the run has a
+// sampled-error check.
 int Problem::poll_tail(bool wait)
 {
-    int st = tail_event(wait);
+    int st = tail_event(run_ev[1], wait);
     if (st <= 0) return st;
     float ms = 0.f;
     HIPCHK(hipEventElapsedTime(&ms, run_ev[0], run_ev[1]));
     time_to_eps = ms * 1e-3 + t_first;
     const ProbState S = *hS_pinned;
-    if (S.err) return set_err(S.err, "device reported error %d", S.err);
+    const int serr = S.err ? S.err : hm->singular ? TT_ESINGULAR : 0;
+    if (serr) return set_err(serr, "device reported error %d", serr);
     finalize(S, ranks_now);
     sweep_launches = 0;
     sweep_kernel_s = sweep_phase_s = 0;
@@ -876,26 +923,7 @@ int Problem::poll_tail(bool wait)
             sweep_phase_s = c * 1e-3;
         }
     }
-    const int64_t R = verify_samples();
-    if (R > 0) {
-        // a13: sampled relative error over an independent SplitMix64(seed + 1)
-        // set; with restarts on, every sample's error as well
-        double *serr = nullptr;
-        if (restarts_on()) {
-            if (serr_cap < R) {
-                if ((st = dalloc((void **)&d_serr, sizeof(double) * R)) != TT_OK) return st;
-                serr_cap = R;
-            }
-            serr = d_serr;
-        }
-        k_verify<<<NBV, NT, 0, stream>>>(dP, d_cores, R, opt.seed + 1, d_part, serr);
-        HIPCHK(hipGetLastError());
-        HIPCHK(hipMemcpyAsync(h_part, d_part, sizeof(double) * 2 * NBV, hipMemcpyDeviceToHost, stream));
-        HIPCHK(hipEventRecord(run_ev[2], stream));
-        phase = PH_VERIFY;
-    } else {
-        phase = PH_DONE;
-    }
+    phase = verify_samples() > 0 ? PH_VERIFY : PH_DONE;
     return 1;
 }
 
@@ -903,7 +931,7 @@ int Problem::poll_tail(bool wait)
 // with FP64 sweeps.
 int Problem::poll_verify(bool wait)
 {
-    int st = tail_event(wait);
+    int st = tail_event(run_ev[2], wait);
     if (st <= 0) return st;
     // partial sums of the NBV workgroups, added in order on the host
     double num = 0.0, den = 0.0;
@@ -1176,6 +1204,7 @@ int Problem::prepare()
                       std::memcmp(alloc_grid, grid, sizeof grid) != 0)) {
         for (void *p : allocs) (void)hipFree(p);
         allocs.clear();
+        slab_left = 0;
         if (hm) { (void)hipHostFree(hm); hm = nullptr; }
         allocated = false;
     }
@@ -1268,6 +1297,105 @@ struct ErrBufs {
     double *x = nullptr, *y = nullptr;   // f and TT values, R each
     double *part = nullptr;         // 2 kErrParts partial sums
 };
+
+// One workspace of sampled-error checks is kept between calls (making and
+// freeing four buffers took 60 us of a million-sample check's 165), at most
+// kErrKeep bytes, until the last handle is destroyed.  A call uses it under
+// the lock and has waited for its stream when it returns.
+constexpr size_t kErrKeep = (size_t)64 << 20;
+static std::mutex g_err_mu;
+static unsigned char *g_err_ws = nullptr;
+static size_t g_err_bytes = 0;
+static int g_err_dev = -1;
+static std::atomic<int> g_handles{0};
+
+// Flags in one page of mapped host memory, one per host thread: a short kernel
+// writes its number there when it is done.  (One page for all: a page of each
+// handle's costs the device an address translation per copy, 8 us.)  The page
+// goes with the last handle; a thread past the last flag gets none.
+static std::mutex g_done_mu;
+static int *g_done_page = nullptr, *g_done_dev = nullptr;
+static hipStream_t g_done_stream = nullptr;
+static int g_done_device = -1;
+constexpr int kDoneSlots = 1024;
+static bool g_done_used[kDoneSlots];
+
+struct DoneSlot {
+    int at = -1;
+    ~DoneSlot()
+    {
+        if (at < 0) return;
+        std::lock_guard<std::mutex> lk(g_done_mu);
+        g_done_used[at] = false;
+    }
+};
+
+// The calling thread's flag; stream: replaced by the shared one if it is a
+// handle's own and on the same device.
+static bool done_slot(int **flag, int **dflag, bool own, hipStream_t *stream)
+{
+    static thread_local DoneSlot slot;
+    std::lock_guard<std::mutex> lk(g_done_mu);
+    if (!g_done_page) {
+        void *h = nullptr, *d = nullptr;
+        if (hipHostMalloc(&h, sizeof(int) * kDoneSlots,
+                          hipHostMallocMapped | hipHostMallocCoherent | hipHostMallocPortable) != hipSuccess) {
+            (void)hipGetLastError();
+            return false;
+        }
+        if (hipHostGetDevicePointer(&d, h, 0) != hipSuccess) {
+            (void)hipGetLastError();
+            (void)hipHostFree(h);
+            return false;
+        }
+        std::memset(h, 0, sizeof(int) * kDoneSlots);
+        if (hipGetDevice(&g_done_device) != hipSuccess ||
+            hipStreamCreateWithFlags(&g_done_stream, hipStreamNonBlocking) != hipSuccess) {
+            (void)hipGetLastError();
+            (void)hipHostFree(h);
+            g_done_stream = nullptr;
+            return false;
+        }
+        g_done_page = (int *)h;
+        g_done_dev = (int *)d;
+    }
+    for (int i = 0; slot.at < 0 && i < kDoneSlots; ++i)
+        if (!g_done_used[i]) {
+            g_done_used[i] = true;
+            slot.at = i;
+        }
+    int dev = -1;
+    if (slot.at < 0 || hipGetDevice(&dev) != hipSuccess || (own && dev != g_done_device)) return false;
+    if (own) *stream = g_done_stream;
+    *flag = g_done_page + slot.at;
+    *dflag = g_done_dev + slot.at;
+    return true;
+}
+
+// A number no flag holds: they differ by 2^32 copies at least.
+static int next_done_number()
+{
+    static std::atomic<unsigned> number{0};
+    unsigned v = number.fetch_add(1) + 1;
+    if (v == 0) v = number.fetch_add(1) + 1;
+    return (int)v;
+}
+
+static void free_done_page()                    // no handle is left
+{
+    std::lock_guard<std::mutex> lk(g_done_mu);
+    if (g_done_stream) (void)hipStreamDestroy(g_done_stream);
+    g_done_stream = nullptr;
+    if (g_done_page) (void)hipHostFree(g_done_page);
+    g_done_page = g_done_dev = nullptr;
+}
+
+static void free_err_ws()                       // with the lock held
+{
+    if (g_err_ws) (void)hipFree(g_err_ws);
+    g_err_ws = nullptr;
+    g_err_bytes = 0;
+}
 
 static int sampled_error_on(Problem &P, int64_t R, uint64_t seed, const ErrBufs &b, double *err)
 {
@@ -1387,6 +1515,7 @@ tt_cross_h tt_cross_create(int d, const int32_t *n, double eps, int fn_id, const
     for (int j = 0; j < d; ++j) P.n[j] = n[j];
     P.eps = eps;
     tt_options_default(&P.opt);
+    g_handles.fetch_add(1);
     return h;
 }
 
@@ -1517,6 +1646,22 @@ int64_t tt_cross_get_cores(tt_cross_h h, double *out, int64_t cap, int on_device
     if (!P.ran) return set_err(TT_ESTATE, "no completed run");
     if (!out) return P.cores_len;
     if (cap < P.cores_len) return set_err(TT_EINVAL, "cap %lld < %lld", (long long)cap, (long long)P.cores_len);
+    int *flag = nullptr, *dflag = nullptr;
+    hipStream_t on = P.stream;
+    if (on_device && P.cores_len <= COPY_ONE && done_slot(&flag, &dflag, P.own_stream, &on)) {
+        const int number = next_done_number();
+        k_copy_one<<<1, 1024, 0, on>>>(P.d_cores, out, (int)P.cores_len, dflag, number);
+        HIPCHK(hipGetLastError());
+        // a short spin on the flag; past it (earlier work on the stream, or a
+        // failure) the stream is waited for
+        const auto t0 = std::chrono::steady_clock::now();
+        while (__atomic_load_n(flag, __ATOMIC_ACQUIRE) != number)
+            if (std::chrono::steady_clock::now() - t0 > std::chrono::microseconds(100)) {
+                HIPCHK(hipStreamSynchronize(on));
+                break;
+            }
+        return P.cores_len;
+    }
     HIPCHK(hipMemcpyAsync(out, P.d_cores, sizeof(double) * P.cores_len,
                           on_device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost, P.stream));
     HIPCHK(hipStreamSynchronize(P.stream));
@@ -1647,17 +1792,36 @@ int tt_cross_sampled_error(tt_cross_h h, int64_t R, uint64_t seed, double *err)
     Problem &P = h->p;
     if (!P.ran) return set_err(TT_ESTATE, "no completed run");
     if (R < 1) return set_err(TT_EINVAL, "R must be >= 1");
+    const size_t bi = kScrAlign(sizeof(int) * (size_t)R * P.d), bx = kScrAlign(sizeof(double) * (size_t)R),
+                 need = bi + 2 * bx + sizeof(double) * 2 * kErrParts;
+    // the workspace kept between checks, if it can hold this one and no other
+    // thread's check is using it; else buffers of the call's own
+    std::unique_lock<std::mutex> lk(g_err_mu, std::try_to_lock);
+    int dev = -1;
+    const bool keep = lk.owns_lock() && need <= kErrKeep && hipGetDevice(&dev) == hipSuccess;
+    unsigned char *base = nullptr;
+    if (keep && g_err_ws && g_err_dev == dev && g_err_bytes >= need) {
+        base = g_err_ws;
+    } else {
+        if (keep) free_err_ws();
+        const hipError_t e = hipMalloc(&base, need);
+        if (e != hipSuccess) {
+            (void)hipGetLastError();
+            return set_err(TT_ENOMEM, "sampled error: %s", hipGetErrorString(e));
+        }
+        if (keep) {
+            g_err_ws = base;
+            g_err_bytes = need;
+            g_err_dev = dev;
+        }
+    }
     ErrBufs b;
-    hipError_t e = hipMalloc(&b.idx, sizeof(int) * R * P.d);
-    if (e == hipSuccess) e = hipMalloc(&b.x, sizeof(double) * R);
-    if (e == hipSuccess) e = hipMalloc(&b.y, sizeof(double) * R);
-    if (e == hipSuccess) e = hipMalloc(&b.part, sizeof(double) * 2 * kErrParts);
-    int st = (e == hipSuccess) ? sampled_error_on(P, R, seed, b, err)
-                               : set_err(TT_ENOMEM, "sampled error: %s", hipGetErrorString(e));
-    if (b.idx) (void)hipFree(b.idx);
-    if (b.x) (void)hipFree(b.x);
-    if (b.y) (void)hipFree(b.y);
-    if (b.part) (void)hipFree(b.part);
+    b.idx = (int *)base;
+    b.x = (double *)(base + bi);
+    b.y = (double *)(base + bi + bx);
+    b.part = (double *)(base + bi + 2 * bx);
+    const int st = sampled_error_on(P, R, seed, b, err);
+    if (!keep) (void)hipFree(base);
     return st;
 }
 
@@ -1686,7 +1850,7 @@ int tt_cross_sampled_error_noalloc(tt_cross_h h, int64_t R, uint64_t seed, doubl
 namespace ttc {
 // Device tables of the functions that bulk evaluation saw last, so that
 // repeated evaluations of one function upload nothing.  A call holds the lock
-// until its kernel has finished (it ends with a device synchronisation), so
+// until its kernel has finished (it waits for the null stream), so
 // no table is replaced while a kernel reads it.  At most kEvalCacheEntries
 // tables of at most kEvalCacheBytes each are kept, until the process ends.
 namespace {
@@ -1696,9 +1860,10 @@ struct EvalKey {
     int fn_id = 0, d = 0;
     std::vector<int32_t> n;
     std::vector<double> params;
-    bool operator==(const EvalKey &o) const
+    bool is(int fn, int dd, const int32_t *nn, const double *pp, int np) const
     {
-        return fn_id == o.fn_id && d == o.d && n == o.n && params == o.params;
+        return fn_id == fn && d == dd && std::equal(n.begin(), n.end(), nn) && (int)params.size() == np &&
+               std::equal(params.begin(), params.end(), pp);
     }
 };
 struct EvalEntry {
@@ -1710,7 +1875,7 @@ std::mutex g_eval_mu;
 std::vector<std::unique_ptr<EvalEntry>> g_eval_cache;
 uint64_t g_eval_clock = 0;
 hipEvent_t g_eval_ev[2] = {nullptr, nullptr};   // attached to the last evaluation's dispatch
-double g_eval_last_ms = -1.0;
+bool g_eval_done = false;
 }  // namespace
 
 // Bulk evaluation behind tt_fn_eval (V = double) and tt_fn_eval_f32.
@@ -1719,9 +1884,20 @@ static int fn_eval_impl(int fn_id, int d, const int32_t *n, const double *params
                         const int32_t *idx, V *out, int on_device)
 {
     g_err.clear();
+    std::unique_lock<std::mutex> lk(g_eval_mu);
+    EvalEntry *ent = nullptr;
+    if (d >= 2 && d <= TT_MAX_D && n && nparams >= 0 && (nparams == 0 || params))
+        for (auto &x : g_eval_cache)
+            if (x->key.is(fn_id, d, n, params, nparams)) { ent = x.get(); break; }
+    // a function seen lately is known to be valid, and its tables are built
     FnHost fresh;
-    int st = build_fn(fn_id, d, n, params, nparams, fresh);
-    if (st) return st;
+    int st = TT_OK;
+    if (!ent) {
+        lk.unlock();
+        if ((st = build_fn(fn_id, d, n, params, nparams, fresh)) != TT_OK) return st;
+    } else {
+        lk.unlock();
+    }
     if (m < 0 || (m > 0 && (!idx || !out))) return set_err(TT_EINVAL, "bad arguments");
     if (m == 0) return TT_OK;
     if (!on_device)
@@ -1729,15 +1905,12 @@ static int fn_eval_impl(int fn_id, int d, const int32_t *n, const double *params
             for (int j = 0; j < d; ++j)
                 if (idx[t * d + j] < 0 || idx[t * d + j] >= n[j])
                     return set_err(TT_EINVAL, "index %lld,%d out of range", (long long)t, j);
-    std::lock_guard<std::mutex> lk(g_eval_mu);
-    EvalKey key;
-    key.fn_id = fn_id;
-    key.d = d;
-    key.n.assign(n, n + d);
-    if (nparams > 0) key.params.assign(params, params + nparams);
-    EvalEntry *ent = nullptr;
+    lk.lock();
+    // (another thread may have changed the cache meanwhile)
+    ent = nullptr;
     for (auto &x : g_eval_cache)
-        if (x->key == key) { ent = x.get(); break; }
+        if (x->key.is(fn_id, d, n, params, nparams)) { ent = x.get(); break; }
+    if (!ent && fresh.dev.d == 0 && (st = build_fn(fn_id, d, n, params, nparams, fresh)) != TT_OK) return st;
     FnHost *fhp = &fresh;
     if (ent) {
         fhp = &ent->fh;
@@ -1749,7 +1922,10 @@ static int fn_eval_impl(int fn_id, int d, const int32_t *n, const double *params
             g_eval_cache.erase(lru);
         }
         auto e = std::make_unique<EvalEntry>();
-        e->key = std::move(key);
+        e->key.fn_id = fn_id;
+        e->key.d = d;
+        e->key.n.assign(n, n + d);
+        if (nparams > 0) e->key.params.assign(params, params + nparams);
         e->fh = std::move(fresh);
         if ((st = upload_fn(e->fh)) != TT_OK) { e->fh.free_device(); return st; }
         ent = e.get();
@@ -1775,10 +1951,8 @@ static int fn_eval_impl(int fn_id, int d, const int32_t *n, const double *params
     for (hipEvent_t &ev : g_eval_ev)
         if (e == hipSuccess && !ev) e = hipEventCreate(&ev);
     if (e == hipSuccess) e = launch_fn_eval<V>(fh.dev, m, didx, dout, nullptr, g_eval_ev[0], g_eval_ev[1]);
-    if (e == hipSuccess) e = hipDeviceSynchronize();
-    float ms = 0.0f;
-    if (e == hipSuccess) e = hipEventElapsedTime(&ms, g_eval_ev[0], g_eval_ev[1]);
-    if (e == hipSuccess) g_eval_last_ms = ms;
+    if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
+    if (e == hipSuccess) g_eval_done = true;    // its time is read when it is asked for
     if (e == hipSuccess && !on_device) e = hipMemcpy(out, dout, sizeof(V) * m, hipMemcpyDeviceToHost);
     if (ti) (void)hipFree(ti);
     if (to) (void)hipFree(to);
@@ -1806,8 +1980,10 @@ int tt_fn_eval_last_kernel_ms(double *ms)
 {
     if (!ms) return set_err(TT_EINVAL, "ms is NULL");
     std::lock_guard<std::mutex> lk(g_eval_mu);
-    if (g_eval_last_ms < 0.0) return set_err(TT_ESTATE, "no bulk evaluation has completed");
-    *ms = g_eval_last_ms;
+    if (!g_eval_done) return set_err(TT_ESTATE, "no bulk evaluation has completed");
+    float t = 0.0f;
+    HIPCHK(hipEventElapsedTime(&t, g_eval_ev[0], g_eval_ev[1]));
+    *ms = t;
     return TT_OK;
 }
 
@@ -1817,6 +1993,13 @@ void tt_cross_destroy(tt_cross_h h)
     // a run in flight is finished first: its kernels use the buffers
     if (h->p.busy()) (void)h->p.advance(true);
     delete h;
+    if (g_handles.fetch_sub(1) == 1) {
+        std::lock_guard<std::mutex> lk(g_err_mu);
+        if (g_handles.load() == 0) {
+            free_err_ws();
+            free_done_page();
+        }
+    }
 }
 
 }  // extern "C"

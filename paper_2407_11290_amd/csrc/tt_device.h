@@ -329,6 +329,7 @@ struct HostMirror {                // fine-grained host memory, written by the d
     int stop;
     int err;
     int r[TT_MAX_D + 1];
+    int singular;                  // Alg. 4 met a zero delta^{-1} (set while the state is on its way)
 };
 
 // Partial result of one workgroup of the sample pass (see samples_body).

@@ -66,6 +66,8 @@ struct Problem {
         alloc_split = -1;
     int alloc_grid[TT_MAX_D] = {0};
     std::vector<void *> allocs;
+    char *slab = nullptr;          // small buffers are cut from slabs (in allocs)
+    size_t slab_left = 0;
     ProbDev hP;
     ProbDev *dP = nullptr;
     HostMirror *hm = nullptr;
@@ -86,15 +88,15 @@ struct Problem {
     double sweep_kernel_s = 0, sweep_alg_bytes = 0, new_entries = 0, sweep_phase_s = 0;
     std::vector<hipEvent_t> prof_events;     // 3 per sweep when profiling
     hipEvent_t run_ev[3] = {nullptr, nullptr, nullptr};  // start / end of a run's device time;
-                                             // end of its last queued copy
-    ProbState *hS_pinned = nullptr;          // pinned host copy of the final device state
-    double *h_part = nullptr;                // pinned host copy of the check's partial sums
+                                             // end of its check
+    void *h_out = nullptr;                   // mapped host memory of the two below
+    ProbState *hS_pinned = nullptr, *d_hS = nullptr;     // mapped host copy of the final state, its device address
+    double *h_part = nullptr, *d_hpart = nullptr;        // the check's partial sums, the same way
     int i0[TT_MAX_D] = {0};
     // sampled-error check and FP32 -> FP64 escalation
     double sampled_err = -1.0;
     int escalated = 0;
     bool force_fp64 = false;       // sweep in FP64 whatever the precision policy says
-    double *d_part = nullptr;      // partial sums of the check (2 * NBV doubles)
     // restarts after false convergence (tt_options.restarts)
     SeedPlan h_plan;               // the point list of the current run and its index sets
     SeedPlan *d_plan = nullptr;    // its device copy (npts = 0: a plain run)
@@ -134,7 +136,7 @@ struct Problem {
     template <typename V> int launch_ahead();
     template <typename V> int poll_sweeps(bool wait);
     template <typename V> int launch_tail();
-    int tail_event(bool wait);
+    int tail_event(hipEvent_t ev, bool wait);
     int poll_tail(bool wait);
     int poll_verify(bool wait);
     int plan_from_points();

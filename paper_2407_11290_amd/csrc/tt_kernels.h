@@ -2624,6 +2624,24 @@ __host__ __device__ inline int make_core_args(int d, const int *n, const int *r,
     return rb + (int)((gd + A4W - 1) / A4W);
 }
 
+// A zero pivot-block residual: in the state (batches copy it after the cores)
+// and in the mirror (a single solve's state leaves beside its cores).
+__device__ inline void note_singular(const ProbDev *P)
+{
+    P->S->err = TT_ESINGULAR;
+    P->hm->singular = 1;
+}
+
+// A single solve's final state to mapped host memory, by the last workgroup
+// of its last core launch: a copy of its own, queued after the cores, took
+// 10 us from their end to the copy's.
+__device__ inline void state_out(const ProbState *S, ProbState *hS)
+{
+    const gptr_t<const uint32_t> src = as_global((const uint32_t *)S);
+    const gptr_t<uint32_t> dst = as_global((uint32_t *)hS);
+    for (int w = threadIdx.x; w < (int)(sizeof(ProbState) / 4); w += A4W) dst[w] = src[w];
+}
+
 // Alg. 4 on one wavefront's rows with T in registers (rk <= RM; RM = 16 fits
 // the register file, 32 does not): lane i holds
 // row i of T for the workgroup's rows, and lanes z < rk also row z of T for
@@ -2785,7 +2803,7 @@ __device__ void cores_body(const ProbDev *__restrict__ P, const CoreArgs &a, dou
     wave_sync();
     if (rk <= 16) {
         // a zero pivot-block residual (delta^{-1} = 0): singular, as in the oracle
-        if (core_alg4_regs<16>(Ap, Ab, st, rk, nr, i0, G + a.goff[u]) && lane == 0) P->S->err = TT_ESINGULAR;
+        if (core_alg4_regs<16>(Ap, Ab, st, rk, nr, i0, G + a.goff[u]) && lane == 0) note_singular(P);
         return;
     }
     bool singular = false;
@@ -2832,13 +2850,15 @@ __device__ void cores_body(const ProbDev *__restrict__ P, const CoreArgs &a, dou
         const int ii = e / rk, z = e - ii * rk;
         Gk[e] = Tb[z * A4W + ii];
     }
-    if (singular && lane == 0) P->S->err = TT_ESINGULAR;
+    if (singular && lane == 0) note_singular(P);
 }
 
 template <int FNS = 0>
-static __global__ void __launch_bounds__(A4W) k_cores(const ProbDev *__restrict__ P, CoreArgs a, double *G)
+static __global__ void __launch_bounds__(A4W) k_cores(const ProbDev *__restrict__ P, CoreArgs a, double *G,
+                                                      ProbState *hS)
 {
-    cores_body<FNS>(P, a, G, blockIdx.x);
+    if (blockIdx.x == gridDim.x - 1) state_out(P->S, hS);
+    else cores_body<FNS>(P, a, G, blockIdx.x);
 }
 
 // ---------------------------------------------------------------------------
@@ -2921,7 +2941,7 @@ __device__ void core_piv_body(const ProbDev *__restrict__ P, const CoreArgs &a, 
         if (lane < z) At[z * CT_LD + lane] = Ap[lane * st + z];
     if (lane == 0) At[0] = a11;
     // a zero pivot-block residual (delta^{-1} = 0): singular, as in the oracle
-    if (singular && lane == 0) P->S->err = TT_ESINGULAR;
+    if (singular && lane == 0) note_singular(P);
 }
 
 template <int FNS = 0>
@@ -3025,9 +3045,10 @@ __device__ void cores_t_body(const ProbDev *__restrict__ P, const CoreArgs &a, d
 
 template <int FNS, int RM>
 static __global__ void __launch_bounds__(A4W) k_cores_t(const ProbDev *__restrict__ P, CoreArgs a, double *G,
-                                                        const double *__restrict__ tab)
+                                                        const double *__restrict__ tab, ProbState *hS)
 {
-    cores_t_body<FNS, RM>(P, a, G, tab, blockIdx.x);
+    if (blockIdx.x == gridDim.x - 1) state_out(P->S, hS);
+    else cores_t_body<FNS, RM>(P, a, G, tab, blockIdx.x);
 }
 
 // ---------------------------------------------------------------------------
@@ -3231,6 +3252,30 @@ static __global__ void __launch_bounds__(NT) k_verify_b(const ProbDev *__restric
 // ---------------------------------------------------------------------------
 // Evaluation helpers.
 // ---------------------------------------------------------------------------
+// Copies m doubles within the device (small cores to a caller's buffer) by one
+// workgroup, which then writes the copy back from its XCD's L2 and tells the
+// host through mapped memory, where a copy command or a kernel and a wait for
+// the stream take 3-7 us more (512 of them after a batch: 7.1 -> 5.4 ms).
+constexpr int64_t COPY_ONE = 32768;          // doubles, at most
+static __global__ void __launch_bounds__(1024) k_copy_one(const double *__restrict__ src, double *__restrict__ dst,
+                                                          int m, int *done, int number)
+{
+    constexpr int U = 8;
+    for (int t0 = threadIdx.x; t0 < m; t0 += U * 1024) {
+        double x[U];
+#pragma unroll
+        for (int j = 0; j < U; ++j) x[j] = src[min(t0 + j * 1024, m - 1)];
+#pragma unroll
+        for (int j = 0; j < U; ++j)
+            if (t0 + j * 1024 < m) dst[t0 + j * 1024] = x[j];
+    }
+    __syncthreads();                         // every wavefront has waited for its stores
+    if (threadIdx.x == 0) {
+        __threadfence_system();
+        __hip_atomic_store(done, number, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+    }
+}
+
 struct TTArgs {
     int d;
     int n[TT_MAX_D];
@@ -3608,28 +3653,39 @@ inline hipError_t launch_tt_eval(const TTArgs &a, const double *G, int64_t m, co
 // start of the round, so the loads of round r+1 are in flight while round r
 // is evaluated.  When the function's per-mode table fits (tab_lds) the
 // workgroup first copies it to LDS, so every table read is an LDS read.
+// VEC (indices 16-byte aligned, as the chunks of ch entries then are): four
+// indices a load.  Bound by HBM: 2^24 FP32 entries of the 6D Maxwellian (470
+// MB) take 101 us, 104 with single loads.
 constexpr int EV_KP = 16;                   // index ints per thread and round
+// Entries of a round: a multiple of four, so that every chunk starts aligned.
+__host__ __device__ inline int fn_eval_chunk(int d) { return (NT * EV_KP / d) & ~3; }
 constexpr int EV_TAB_LDS_MAX = 32768;       // bytes of table copied to LDS, at most
 
 __host__ __device__ inline size_t fn_eval_idx_bytes() { return (size_t)NT * EV_KP * sizeof(int); }
 
-template <typename V>
+template <typename V, bool VEC>
 static __global__ void __launch_bounds__(NT) k_fn_eval(FnDev F, int64_t m, const int *__restrict__ idx,
                                                        V *__restrict__ out, int tab_lds)
 {
     extern __shared__ __align__(16) unsigned char smem_raw[];
     const int d = F.d, tid = threadIdx.x;
-    const int ch = (NT * EV_KP) / d;
+    const int ch = fn_eval_chunk(d);
     const int64_t stride = (int64_t)gridDim.x * ch;
     int *sidx = (int *)smem_raw;
-    int pf[EV_KP];
+    typedef int ivec4 __attribute__((ext_vector_type(4)));
+    ivec4 pf[EV_KP / 4];
     auto fetch = [&](int64_t b) {
         const int nint = (b < m) ? (int)min((int64_t)ch, m - b) * d : 0;
-        const int *src = idx + (b < m ? b : 0) * d;
+        const gptr_t<const int> src = as_global(idx) + (b < m ? b : 0) * d;
 #pragma unroll
-        for (int r = 0; r < EV_KP; ++r) {
-            const int i = tid + r * NT;
-            pf[r] = (i < nint) ? src[i] : 0;
+        for (int r = 0; r < EV_KP / 4; ++r) {
+            const int i = 4 * (tid + r * NT);
+            if (VEC && i + 4 <= nint) {
+                pf[r] = *(gptr_t<const ivec4>)(src + i);
+            } else {
+#pragma unroll
+                for (int j = 0; j < 4; ++j) pf[r][j] = (i + j < nint) ? src[i + j] : 0;
+            }
         }
     };
     auto rounds = [&](const V *tb) {
@@ -3639,7 +3695,7 @@ static __global__ void __launch_bounds__(NT) k_fn_eval(FnDev F, int64_t m, const
             const int cnt = (int)min((int64_t)ch, m - base);
             __syncthreads();                // the previous round's reads of sidx are done
 #pragma unroll
-            for (int r = 0; r < EV_KP; ++r) sidx[tid + r * NT] = pf[r];
+            for (int r = 0; r < EV_KP / 4; ++r) *(ivec4 *)(sidx + 4 * (tid + r * NT)) = pf[r];
             __syncthreads();
             fetch(base + stride);
             for (int e = tid; e < cnt; e += NT) {
@@ -3670,15 +3726,16 @@ inline hipError_t launch_fn_eval(const FnDev &F, int64_t m, const int *idx, V *o
     const size_t tab_bytes = (size_t)F.tab_rows * F.tab_ld * sizeof(V);
     const int tab_lds = (fn_table<V>(F) && tab_bytes > 0 && tab_bytes <= EV_TAB_LDS_MAX) ? 1 : 0;
     const size_t lds = fn_eval_idx_bytes() + (tab_lds ? tab_bytes : 0);
-    const int ch = (NT * EV_KP) / F.d;
+    const int ch = fn_eval_chunk(F.d);
     const int64_t rounds = (m + ch - 1) / ch;
     const unsigned g = (unsigned)std::min<int64_t>(rounds, 2048);
+    auto kern = ((uintptr_t)idx & 15) == 0 ? k_fn_eval<V, true> : k_fn_eval<V, false>;
     if (ev_start && ev_stop) {
         // the events take the dispatch's own start and end timestamps
-        hipExtLaunchKernelGGL(k_fn_eval<V>, dim3(g), dim3(NT), (uint32_t)lds, stream, ev_start, ev_stop, 0u, F, m,
+        hipExtLaunchKernelGGL(kern, dim3(g), dim3(NT), (uint32_t)lds, stream, ev_start, ev_stop, 0u, F, m,
                               idx, out, tab_lds);
     } else {
-        k_fn_eval<V><<<g, NT, lds, stream>>>(F, m, idx, out, tab_lds);
+        kern<<<g, NT, lds, stream>>>(F, m, idx, out, tab_lds);
     }
     return hipGetLastError();
 }
