@@ -254,7 +254,6 @@ void Problem::release()
 {
     for (void *p : allocs) (void)hipFree(p);
     allocs.clear();
-    slab_left = 0;
     for (hipEvent_t e : prof_events) (void)hipEventDestroy(e);
     prof_events.clear();
     if (hm) { (void)hipHostFree(hm); hm = nullptr; }
@@ -273,27 +272,6 @@ int Problem::dalloc(void **p, size_t bytes)
 {
     *p = nullptr;
     if (bytes == 0) bytes = 16;
-    // small buffers (a dozen per unfolding) come from slabs: each allocation
-    // of its own takes some 5 us of a new handle's first run
-    constexpr size_t SMALL = (size_t)32 << 10, SLAB = (size_t)256 << 10;
-    if (bytes <= SMALL) {
-        bytes = (bytes + 255) & ~(size_t)255;
-        if (slab_left < bytes) {
-            void *s = nullptr;
-            const hipError_t es = hipMalloc(&s, SLAB);
-            if (es != hipSuccess) {
-                (void)hipGetLastError();
-                return set_err(TT_ENOMEM, "hipMalloc(%zu) failed: %s", SLAB, hipGetErrorString(es));
-            }
-            allocs.push_back(s);
-            slab = (char *)s;
-            slab_left = SLAB;
-        }
-        *p = slab;
-        slab += bytes;
-        slab_left -= bytes;
-        return TT_OK;
-    }
     hipError_t e = hipMalloc(p, bytes);
     if (e != hipSuccess) {
         *p = nullptr;
@@ -1204,7 +1182,6 @@ int Problem::prepare()
                       std::memcmp(alloc_grid, grid, sizeof grid) != 0)) {
         for (void *p : allocs) (void)hipFree(p);
         allocs.clear();
-        slab_left = 0;
         if (hm) { (void)hipHostFree(hm); hm = nullptr; }
         allocated = false;
     }

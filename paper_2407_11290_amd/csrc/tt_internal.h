@@ -66,8 +66,6 @@ struct Problem {
         alloc_split = -1;
     int alloc_grid[TT_MAX_D] = {0};
     std::vector<void *> allocs;
-    char *slab = nullptr;          // small buffers are cut from slabs (in allocs)
-    size_t slab_left = 0;
     ProbDev hP;
     ProbDev *dP = nullptr;
     HostMirror *hm = nullptr;
