@@ -120,7 +120,7 @@ int Engine::admit(Problem *Q, void *user)
         K.smax = 0;
         D.sh0.lsp[u] = 0;
         D.sh0.soff[u] = acc;
-        D.sh0.ntl[u] = K.RTp * K.CTq;
+        D.sh0.ntl[u] = stored_tiles(K.nk, K.nk1, K.TR);
         acc += D.sh0.ntl[u];
         D.sh0.soff[u + 1] = acc;
     }

@@ -231,16 +231,14 @@ static int pow2_at_least(int x)
 
 // Split one mode into tiles: blocks b = [b*n/C, (b+1)*n/C) (Sec. 3: n_j split
 // evenly into C_j pieces), each cut into chunks of at most T entries.
-static void mode_tiles(int n, int C, int T, std::vector<int> &start, std::vector<int> &len,
-                       std::vector<int> &blk)
+static void mode_tiles(int n, int C, int T, std::vector<int> &start, std::vector<int> &len)
 {
-    start.clear(); len.clear(); blk.clear();
+    start.clear(); len.clear();
     for (int b = 0; b < C; ++b) {
         const int lo = (int)((int64_t)b * n / C), hi = (int)((int64_t)(b + 1) * n / C);
         for (int s = lo; s < hi; s += T) {
             start.push_back(s);
             len.push_back(std::min(T, hi - s));
-            blk.push_back(b);
         }
     }
 }
@@ -391,8 +389,9 @@ int Problem::allocate()
             K.ld = ((K.colcap + 2 * per256 - 1) / (2 * per256)) * (2 * per256) + per256;
         }
         K.rk_cap = rc[k];
-        // tile geometry: rows of mode k, columns of mode k+1.  A tile lies in
-        // one run of i_k (i_{k+1}) inside a subtensor block.  Default height,
+        // tile geometry: rows of mode k, columns of mode k+1.  A new-entry tile
+        // lies in one run of i_k (i_{k+1}) inside a subtensor block; a stored
+        // tile is TR x TS positions (stored_tiles).  Default height,
         // from measured sweeps of shapes: 256 rows when both runs are long
         // (>= 400), where a stored tile (one wavefront's work) gains from
         // streaming longer and the new-entry tiles are still many; 64 rows
@@ -406,7 +405,7 @@ int Problem::allocate()
         };
         const int runr = longest_run(n[k - 1], grid[k - 1]), maxrun = longest_run(n[k], grid[k]);
         int TR = req_tr > 0 ? req_tr : ((runr >= 400 && maxrun >= 400) ? 256 : (d >= 4 && runr >= 100) ? 64 : 32);
-        // stored tiles put 64 / TC rows on a wavefront: TC <= 64
+        // a new-entry tile's columns are at most a wavefront: TC <= 64
         int TC = req_tc > 0 ? req_tc : std::min(64, pow2_at_least(maxrun));
         TC = std::min(pow2_at_least(TC), 64);
         if (req_tr <= 0 && req_tc <= 0) {
@@ -422,14 +421,12 @@ int Problem::allocate()
         // chain of phases, and tall ones left most of the chip idle (3D, n =
         // 1000: 128 tiles of 256 x 64 a sweep)
         const int TRn = std::min(TR, NEW_ROWS);
-        std::vector<int> rs, rl, rb, cs, cl, cb, ms, ml, mb;
-        mode_tiles(n[k - 1], grid[k - 1], TR, rs, rl, rb);
-        mode_tiles(n[k - 1], grid[k - 1], TRn, ms, ml, mb);
-        mode_tiles(n[k], grid[k], TC, cs, cl, cb);
+        std::vector<int> cs, cl, ms, ml;
+        mode_tiles(n[k - 1], grid[k - 1], TRn, ms, ml);
+        mode_tiles(n[k], grid[k], TC, cs, cl);
         if (!rook && sweep_lds_bytes(rc[k], TR, TC, w) + lds_static > (size_t)lds_limit)
             return set_err(TT_EINVAL, "tile %dx%d with rank cap %d needs more LDS than a workgroup has (%d B)",
                            TR, TC, rc[k], lds_limit);
-        K.RTp = (int)rs.size();
         K.CTq = (int)cs.size();
         K.RTn = (int)ms.size();
         K.TRn = TRn;
@@ -440,21 +437,15 @@ int Problem::allocate()
         tileTR[u] = TR;
         tileTC[u] = TC;
         int *tabs;
-        if ((st = dalloc((void **)&tabs, sizeof(int) * (3 * (rs.size() + cs.size()) + 2 * ms.size()))) != TT_OK) return st;
+        if ((st = dalloc((void **)&tabs, sizeof(int) * 2 * (cs.size() + ms.size()))) != TT_OK) return st;
         std::vector<int> all;
-        all.insert(all.end(), rs.begin(), rs.end());
-        all.insert(all.end(), rl.begin(), rl.end());
-        all.insert(all.end(), rb.begin(), rb.end());
         all.insert(all.end(), cs.begin(), cs.end());
         all.insert(all.end(), cl.begin(), cl.end());
-        all.insert(all.end(), cb.begin(), cb.end());
         all.insert(all.end(), ms.begin(), ms.end());
         all.insert(all.end(), ml.begin(), ml.end());
         HIPCHK(hipMemcpy(tabs, all.data(), sizeof(int) * all.size(), hipMemcpyHostToDevice));
-        const int R = K.RTp, Cc = K.CTq;
-        K.rt_start = tabs; K.rt_len = tabs + R; K.rt_blk = tabs + 2 * R;
-        K.ct_start = tabs + 3 * R; K.ct_len = tabs + 3 * R + Cc; K.ct_blk = tabs + 3 * R + 2 * Cc;
-        K.nt_start = K.ct_blk + Cc; K.nt_len = K.nt_start + K.RTn;
+        K.ct_start = tabs; K.ct_len = tabs + K.CTq;
+        K.nt_start = K.ct_len + K.CTq; K.nt_len = K.nt_start + K.RTn;
         const int rk = rc[k];
         if (rook) {
             // factors W (rows x rank) and U (rank x columns) instead of the residual
@@ -488,7 +479,8 @@ int Problem::allocate()
         if ((st = dalloc((void **)&K.piv64, sizeof(double) * rk)) != TT_OK) return st;
         if ((st = dalloc((void **)&K.Wp64, sizeof(double) * rcmax * rcmax)) != TT_OK) return st;
         if ((st = dalloc((void **)&K.Up64, sizeof(double) * rcmax * rcmax)) != TT_OK) return st;
-        K.cand_cap = rook ? K.nrb * K.ncb : rc[k - 1] * ((K.RTp << K.smax) + K.RTn) * (rc[k + 1] * K.CTq) + 1;
+        K.cand_cap = rook ? K.nrb * K.ncb
+                          : (stored_tiles(K.rowcap, K.colcap, K.TR) << K.smax) + rc[k - 1] * K.RTn * (rc[k + 1] * K.CTq) + 1;
         if ((st = dalloc((void **)&K.cand, sizeof(Cand) * K.cand_cap)) != TT_OK) return st;
         if ((st = dalloc((void **)&K.hist, sizeof(double) * hist_cap)) != TT_OK) return st;
         cores_cap += (int64_t)rc[k - 1] * n[k - 1] * rc[k];
@@ -519,9 +511,9 @@ int Problem::allocate()
     for (int u = 0; u < d - 1; ++u) {
         const KDev &K = H.kd[u];
         KTile &T = H.kt[u];
-        T.nk = K.nk; T.nk1 = K.nk1; T.ld = K.ld; T.RTp = K.RTp; T.CTq = K.CTq; T.RTn = K.RTn;
-        T.TRn = K.TRn; T.TC = K.TC; T.TR = K.TR; T.pad = 0; T.nt_start = K.nt_start; T.nt_len = K.nt_len;
-        T.rt_start = K.rt_start; T.rt_len = K.rt_len; T.ct_start = K.ct_start; T.ct_len = K.ct_len;
+        T.nk = K.nk; T.nk1 = K.nk1; T.ld = K.ld; T.CTq = K.CTq; T.RTn = K.RTn;
+        T.TRn = K.TRn; T.TC = K.TC; T.TR = K.TR; T.nt_start = K.nt_start; T.nt_len = K.nt_len;
+        T.ct_start = K.ct_start; T.ct_len = K.ct_len;
         T.E = K.E; T.rpiv = K.rpiv; T.cpiv = K.cpiv; T.rho = K.rho; T.gam = K.gam; T.piv = K.piv;
         T.Ifull = K.Ifull; T.Jfull = K.Jfull;
         T.Ipre = u >= 1 ? H.kd[u - 1].Ifull : nullptr;
@@ -536,8 +528,9 @@ int Problem::allocate()
         H.sh0.RT[u] = H.sh0.RTs[u] = K.RTn;
         H.sh0.CT[u] = H.sh0.CTs[u] = K.CTq;
         H.sh0.soff[u] = acc;
-        H.sh0.lsp[u] = stored_split(K.RTp * K.CTq, d - 1, K.smax);
-        H.sh0.ntl[u] = (K.RTp * K.CTq) << H.sh0.lsp[u];
+        const int nst = stored_tiles(K.nk, K.nk1, K.TR);
+        H.sh0.lsp[u] = stored_split(nst, d - 1, K.smax);
+        H.sh0.ntl[u] = nst << H.sh0.lsp[u];
         acc += H.sh0.ntl[u];
         H.sh0.soff[u + 1] = acc;
     }
@@ -689,7 +682,9 @@ template <typename V> int Problem::launch_ahead()
             sweep_units(K, rub, rst, k, nk, nnew, nst);
             // the commit's first round of candidates: at most this many
             a.cand[u] = K.cand;
-            a.ntl_max[u] = rook ? K.nrb * K.ncb : rub[k - 1] * (K.RTn + (K.RTp << K.smax)) * rub[k + 1] * K.CTq + 1;
+            a.ntl_max[u] = rook ? K.nrb * K.ncb
+                                : (stored_tiles(rub[k - 1] * K.nk, K.nk1 * rub[k + 1], K.TR) << K.smax) +
+                                      rub[k - 1] * K.RTn * rub[k + 1] * K.CTq + 1;
             units += nnew + (nst + NT / 64 - 1) / (NT / 64);
             lds = std::max(lds, sweep_lds_bytes(rub[k], K.TRn, K.TC, sizeof(V)));
         }

@@ -10,7 +10,6 @@
 namespace ttc {
 
 constexpr int NT = 256;                    // threads per workgroup (4 wave64)
-constexpr int TT_TILE_ROWS_MAX = 256;      // largest tile extent along the rows
 constexpr double PI = 3.14159265358979323846;
 constexpr uint64_t SM64_GAMMA = 0x9E3779B97F4A7C15ULL;
 constexpr int TT_ROOK_ITERS = 8;           // rounds of Alg. 1's loop in the split search's fixed
@@ -211,13 +210,12 @@ struct KDev {
     int rowcap, colcap;           // capacity of the stored superblock
     int ld;                       // row pitch of E in entries (colcap padded off powers of two)
     int rk_cap;                   // pivot capacity of this unfolding
-    int RTp, CTq;                 // stored row tiles per prefix, column tiles per suffix
+    int CTq;                      // column tiles per suffix
     int RTn, TRn;                 // new-entry row tiles per prefix and their largest height
-    int TR, TC;                   // largest extent of a stored tile (its width is any tile's)
+    int TR, TC;                   // height of a stored tile, width of a new-entry tile
     int smax;                     // log2 of the parts a stored tile can be searched in
-    const int *rt_start, *rt_len, *rt_blk;    // per stored row tile within a prefix
-    const int *nt_start, *nt_len;             // per new-entry row tile within a prefix
-    const int *ct_start, *ct_len, *ct_blk;    // per column tile within a suffix
+    const int *nt_start, *nt_len; // per new-entry row tile within a prefix
+    const int *ct_start, *ct_len; // per column tile within a suffix
     void *E;                      // residual / frozen factors, rowcap x colcap, row-major, pitch ld
     uint8_t *rpiv, *cpiv;         // z+1 on the row / column of pivot z, else 0 (padded to whole words)
     int *Ifull;                   // I_{<=k}: rcap tuples of k indices
@@ -245,8 +243,8 @@ struct KDev {
 // its neighbours' index-tuple arrays; kept apart and small, so that a search
 // workgroup loads every unfolding's copy in its first round of loads.
 struct KTile {
-    int nk, nk1, ld, RTp, CTq, RTn, TRn, TC, TR, pad;
-    const int *rt_start, *rt_len, *nt_start, *nt_len, *ct_start, *ct_len;
+    int nk, nk1, ld, CTq, RTn, TRn, TC, TR;
+    const int *nt_start, *nt_len, *ct_start, *ct_len;
     void *E;
     const uint8_t *rpiv, *cpiv;
     const int *rho, *gam;
@@ -296,6 +294,21 @@ struct SweepShape {
     int noff[TT_MAX_D + 1], soff[TT_MAX_D + 1];
 };
 constexpr int SHAPE_WORDS = (int)(sizeof(SweepShape) / sizeof(int));
+
+// Stored entries are searched in tiles of positions, TR rows by TS columns,
+// whatever blocks, prefixes and suffixes they cross: an entry's update and the
+// best of all entries do not depend on the tile.  So no tile is cut short at
+// the end of a block or a mode's run: the wavefront keeps 64 columns, and a
+// row of a tile is read in whole lines.  Tiles inside one block and one prefix
+// left lanes and loads idle (8 x 8 entries at 16 points a mode in two blocks;
+// 15 of 16 column tiles whole at 1000): 3D n = 1000 to rank 25 took 2.67 ms
+// and takes 2.48, the 3d3v Maxwellian of 800 x 400 points 3.56 -> 3.44 ms, a
+// mixed batch of 512 problems 14.1 -> 13.6 ms, 6D n = 64 stays at 0.38 ms.
+constexpr int TS = 64;
+__host__ __device__ inline int stored_tiles(int rows, int cols, int TR)
+{
+    return ((rows + TR - 1) / TR) * ((cols + TS - 1) / TS);
+}
 
 // Parts (2^l) a sweep searches each stored tile of an unfolding in: tall
 // tiles stream best when there are many, but a wavefront takes its tile's

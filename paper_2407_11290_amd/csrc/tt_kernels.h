@@ -163,7 +163,7 @@ inline void sweep_units(const KDev &K, const int *rub, const int *rst, int k, in
 {
     const int all = rub[k - 1] * K.RTn * rub[k + 1] * K.CTq;
     nnew = all - std::min(all, rst[k - 1] * K.RTn * rst[k + 1] * K.CTq);
-    nst = std::min(rub[k - 1], rst[k - 1]) * K.RTp * std::min(rub[k + 1], rst[k + 1]) * K.CTq;
+    nst = stored_tiles(std::min(rub[k - 1], rst[k - 1]) * K.nk, K.nk1 * std::min(rub[k + 1], rst[k + 1]), K.TR);
     nst <<= stored_split(nst, nk, K.smax);
 }
 
@@ -179,20 +179,16 @@ struct TileGeom {
 };
 
 // Part `part` of 2^lsp of stored tile (R, C); nrows may come out as 0.
-__device__ inline TileGeom tile_geom(const KTile &K, int u, int R, int C, int part, int lsp)
+__device__ inline TileGeom tile_geom(const KTile &K, const KSweep &s, int u, int R, int C, int part, int lsp)
 {
     TileGeom g;
-    g.u = u; g.R = R; g.C = C;
-    g.p = R / K.RTp;
-    const int t = R - g.p * K.RTp;
-    g.q = C / K.CTq;
-    const int tc = C - g.q * K.CTq;
     const int h = (K.TR + (1 << lsp) - 1) >> lsp;
-    g.ik0 = K.rt_start[t] + part * h;
-    g.nrows = max(min(K.rt_len[t] - part * h, h), 0);
-    g.ik10 = K.ct_start[tc]; g.ncols = K.ct_len[tc];
-    g.row0 = g.p * K.nk + g.ik0;
-    g.col0 = g.q * K.nk1 + g.ik10;
+    g.u = u; g.R = R; g.C = C;
+    g.row0 = R * K.TR + part * h;
+    g.nrows = max(min(min(h, K.TR - part * h), s.nr_st - g.row0), 0);
+    g.col0 = C * TS;
+    g.ncols = min(TS, s.nc_st - g.col0);
+    g.ik0 = g.ik10 = g.p = g.q = 0;
     return g;
 }
 
@@ -213,7 +209,9 @@ __device__ inline void block_best_t0(double &v, uint64_t &key, double &sv)
 }
 
 // Stored residuals, one wavefront per tile: apply the newest pivot and search
-// (an unfolding without a new pivot has no stored tiles to visit), in batches of B * (64 / TC) rows.  A 64-row chunk's first
+// (an unfolding without a new pivot has no stored tiles to visit), in batches
+// of B rows a lane (several rows side by side where the whole superblock is
+// narrower than the wavefront).  A 64-row chunk's first
 // batch goes out in one round of loads with the chunk's row masks and W
 // factors (and, for the first chunk, the column's mask and pivot-row entry),
 // from addresses that are always valid, and nothing loaded is used before
@@ -232,8 +230,9 @@ __device__ void stored_tile_wave(const KTile &K, const KSweep &ks, const TileGeo
     g.row0 = __builtin_amdgcn_readfirstlane(gv.row0);
     g.col0 = __builtin_amdgcn_readfirstlane(gv.col0);
     const int lane = threadIdx.x & 63;
-    const int TC = K.TC, rpw = 64 / TC;
-    const int tr = lane / TC, tcol = lane - tr * TC;
+    // several rows at a time where the superblock is narrower than a tile
+    const int tl = ks.nc_st > 32 ? 6 : ks.nc_st > 16 ? 5 : ks.nc_st > 8 ? 4 : 3, rpw = 64 >> tl;
+    const int tr = lane >> tl, tcol = lane & ((1 << tl) - 1);
     const bool colok = tcol < g.ncols;
     const gptr_t<V> E = as_global((V *)K.E);
     const gptr_t<const uint32_t> rpiv_w = as_global((const uint32_t *)K.rpiv);
@@ -982,7 +981,7 @@ __device__ void sweep_body(const ProbDev *__restrict__ P, const ProbState *S, in
             if (st < nst) {
                 int u = 0;
                 while (u + 1 < nk && st >= sh.soff[u + 1]) ++u;
-                const int idx = st - sh.soff[u], CTs = sh.CTs[u], lsp = __builtin_amdgcn_readfirstlane(sh.lsp[u]);
+                const int idx = st - sh.soff[u], CTs = (ks[u].nc_st + TS - 1) / TS, lsp = __builtin_amdgcn_readfirstlane(sh.lsp[u]);
                 const int tile = idx >> lsp;
                 // the tile is the wavefront's (values read from LDS are
                 // per-lane to the compiler): uniform geometry and loop counts
@@ -991,7 +990,7 @@ __device__ void sweep_body(const ProbDev *__restrict__ P, const ProbState *S, in
                 const int C = __builtin_amdgcn_readfirstlane(tile - R * CTs);
                 const int part = __builtin_amdgcn_readfirstlane(idx - (tile << lsp));
                 const KTile &K = P->kt[u];
-                const TileGeom g = tile_geom(K, u, R, C, part, lsp);
+                const TileGeom g = tile_geom(K, ks[u], u, R, C, part, lsp);
 #ifdef TT_STAMPS
                 // wave 0's first stored tile: geometry known, tile done
                 const bool first_st = rec && wid == 0 && rec[11] == 0;
@@ -1307,7 +1306,7 @@ __device__ void commit_body(const ProbDev *__restrict__ P, ProbState *S, int swe
             // the descriptor fields the next shapes need
             s_geo[u][0] = K.nk;
             s_geo[u][1] = K.nk1;
-            s_geo[u][2] = K.RTp;
+            s_geo[u][2] = K.TR;
             s_geo[u][3] = K.CTq;
             s_geo[u][4] = K.RTn;
             s_geo[u][5] = K.smax;
@@ -1360,7 +1359,7 @@ __device__ void commit_body(const ProbDev *__restrict__ P, ProbState *S, int swe
         int nn = 0, ns = 0;
         if (u < nk) {
             const int k = u + 1;
-            const int knk = s_geo[u][0], knk1 = s_geo[u][1], kRTp = s_geo[u][2], kCTq = s_geo[u][3],
+            const int knk = s_geo[u][0], knk1 = s_geo[u][1], kTR = s_geo[u][2], kCTq = s_geo[u][3],
                       kRTn = s_geo[u][4];
             KSweep n;
             n.rk = s_rnew[k];
@@ -1383,7 +1382,7 @@ __device__ void commit_body(const ProbDev *__restrict__ P, ProbState *S, int swe
             S->sh.CTs[u] = CTs;
             nn = RT * CT - RTs * CTs;
             // unchanged stored entries are not visited
-            ns = s_prop[u] ? s_rold[k - 1] * kRTp * CTs : 0;
+            ns = s_prop[u] ? stored_tiles(ks[u].nr, ks[u].nc, kTR) : 0;
             const int lsp = stored_split(ns, nk, s_geo[u][5]);
             S->sh.lsp[u] = lsp;
             ns <<= lsp;

@@ -107,6 +107,27 @@ def test_tall_tiles_and_large_ranks(n, rows, cols, r, fn):
     _same(g, o)
 
 
+@pytest.mark.parametrize("n,rows,cols,grid", [
+    ([9, 8, 5, 7, 9], 0, 0, 1),                # superblocks of 8, 9, 16, 17 columns and more
+    ([33, 31, 32, 34], 0, 0, 2),               # 31-34 columns at first, blocks of 15-17
+    ([70, 63, 64, 65], 0, 0, 3),               # 63-65
+    ([40, 70, 9], 256, 8, 1),                  # tiles taller than a mode
+    ([40, 21, 50], 3, 64, 4),                  # and shorter than a word of the row masks
+])
+def test_stored_tiles_across_blocks(n, rows, cols, grid):
+    """Stored tiles cross blocks, prefixes and suffixes, and end where the
+    superblock ends: the oracle's bits."""
+    _say("stored tiles", n, rows, cols, grid)
+    params = _sepsum(n, 9, 8)
+    kw = dict(seed=5, precision=PREC_FP64, grid=[grid] * len(n), tile_rows=rows, tile_cols=cols)
+    g, h = (TTCross(n, 1e-9, FN_SEPSUM, params, **kw) for _ in range(2))
+    o = Oracle(n, 1e-9, FN_SEPSUM, params, seed=5)
+    assert g.run() == o.run()
+    _same(g, o)
+    batch_run([h])
+    _same(h, o)
+
+
 @pytest.mark.parametrize("fn,n,caps,prec", [
     (FN_MAXWELL_2D2V, [33, 18, 70, 21], [7, 4, 9], PREC_FP64),
     (FN_MAXWELL_2D2V, [20, 65, 17, 129], [5, 5, 5], PREC_FP32),
