@@ -433,7 +433,7 @@ int Problem::allocate()
         K.TR = TR;
         K.TC = TC;
         K.smax = 0;
-        while ((64 << K.smax) <= TR) ++K.smax;
+        while ((32 << K.smax) <= TR) ++K.smax;
         tileTR[u] = TR;
         tileTC[u] = TC;
         int *tabs;

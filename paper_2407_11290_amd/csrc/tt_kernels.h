@@ -11,12 +11,14 @@
 // columns are never searched, so nothing else is needed.
 //
 // One search sweep over all unfoldings is two launches:
-//   k_sweep   one workgroup per tile of every superblock; a tile lies inside a
-//             single subtensor block and a single prefix/suffix.  A stored tile
-//             applies the newest pivot (rank-1 update); a new tile evaluates
+//   k_sweep   one workgroup per tile of new entries, which lies inside a
+//             single subtensor block and a single prefix/suffix: it evaluates
 //             the generating function on its entries and eliminates every
-//             pivot from them in insertion order.  Both fuse the |residual|
-//             argmax of the tile (the block-local pivot of Alg. 3).
+//             pivot from them in insertion order, on the matrix cores.  One
+//             wavefront per tile of stored entries, anywhere in the
+//             superblock: it applies the newest pivot (rank-1 update).  Both
+//             fuse the |residual| argmax of the tile; the best of the tiles
+//             is the best of the block-local pivots of Alg. 3.
 //   k_commit  one workgroup for all unfoldings: best of the local pivots
 //             (Sec. 3.2.1), stop test, append to the nested index sets.
 #pragma once
@@ -3052,7 +3054,7 @@ static __global__ void __launch_bounds__(A4W) k_cores_t(const ProbDev *__restric
 
 // ---------------------------------------------------------------------------
 // Sampled-error check (Sec. 5): over R multi-indices drawn from
-// SplitMix64(seed), the sums of (X - X~)^2 and X^2, one wavefront per sample
+// SplitMix64(seed), the sums of (X - X~)^2 and X^2, a lane group per sample
 // (lane b carries entry b of the running row vector of the TT product).
 // Workgroup blk of nblk writes its two partial sums to part[2*blk..]; the
 // caller adds the nblk pairs in order, so the result does not depend on
