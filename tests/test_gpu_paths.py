@@ -5,7 +5,7 @@ import pytest
 
 from oracle import Oracle, fn_eval as orc_fn_eval
 from paper_2407_11290_amd import FN_HILBERT, FN_MAXWELL_2D2V, FN_MAXWELL_3D3V, FN_SEPSUM, PREC_FP32, PREC_FP64
-from paper_2407_11290_amd.api import TTCross, batch_run
+from paper_2407_11290_amd.api import TTCross, batch_run, fn_eval
 
 pytestmark = pytest.mark.gpu
 
@@ -148,3 +148,21 @@ def test_kinetic_entries_from_tile_parts(fn, n, caps, prec):
         assert np.array_equal(g.history(k).view(np.uint64), h.history(k).view(np.uint64)), k
         assert all(np.array_equal(a, b) for a, b in zip(g.pivots(k), h.pivots(k))), k
     assert np.array_equal(g.cores_flat().view(np.uint64), h.cores_flat().view(np.uint64))
+
+
+@pytest.mark.parametrize("n,m", [([32, 17, 9], 1), ([32, 17, 9], 681), ([31, 8, 5, 6], 683), ([9] * 5, 2047), ([32] * 3, 1364)])
+@pytest.mark.parametrize("shift", [0, 1, 2, 3])
+def test_bulk_evaluation_reads_any_alignment(n, m, shift):
+    """Index lists that start on a 16-byte line are read 16 bytes at a time,
+    others word by word: the same values."""
+    _say("bulk evaluation", n, m, shift)
+    torch = pytest.importorskip("torch")
+    rng = np.random.default_rng(shift)
+    idx = np.stack([rng.integers(0, j, m) for j in n], axis=1).astype(np.int32)
+    room = torch.zeros(m * len(n) + 8, dtype=torch.int32, device="cuda")
+    start = (-(room.data_ptr() // 4)) % 4 + shift
+    dev = room[start:start + m * len(n)].view(m, len(n))
+    dev.copy_(torch.from_numpy(idx))
+    assert dev.data_ptr() % 16 == 4 * shift and dev.is_contiguous()
+    x = fn_eval(FN_HILBERT, n, dev).cpu().numpy()
+    assert np.array_equal(x, orc_fn_eval(FN_HILBERT, n, idx))
