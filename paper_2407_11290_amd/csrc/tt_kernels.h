@@ -65,10 +65,9 @@ __device__ inline bool better(double a, uint64_t ka, double b, uint64_t kb)
     return a > b || (a == b && ka < kb);
 }
 
-// A workgroup barrier that orders LDS accesses only.  __syncthreads also
-// waits for every global load and store the wavefront has in flight; where
-// what follows reads nothing another thread wrote to device memory, the
-// stores then drain while the workgroup goes on.
+// A workgroup barrier that orders LDS accesses only: the compiler keeps global
+// accesses on their side of __syncthreads, here it may move them across.
+// Neither barrier waits for stores to device memory to finish.
 __device__ inline void lds_barrier()
 {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
@@ -3256,7 +3255,10 @@ static __global__ void __launch_bounds__(NT) k_verify_b(const ProbDev *__restric
 // Copies m doubles within the device (small cores to a caller's buffer) by one
 // workgroup, which then writes the copy back from its XCD's L2 and tells the
 // host through mapped memory, where a copy command or a kernel and a wait for
-// the stream take 3-7 us more (512 of them after a batch: 7.1 -> 5.4 ms).
+// the stream take longer.  Nobody waits for the kernel itself, so the flag may
+// only follow the last store: a workgroup barrier does not wait for stores to
+// device memory, so every wavefront waits for its own (they are in the L2
+// then), and after the barrier one write-back takes all of them to memory.
 constexpr int64_t COPY_ONE = 32768;          // doubles, at most
 static __global__ void __launch_bounds__(1024) k_copy_one(const double *__restrict__ src, double *__restrict__ dst,
                                                           int m, int *done, int number)
@@ -3270,10 +3272,11 @@ static __global__ void __launch_bounds__(1024) k_copy_one(const double *__restri
         for (int j = 0; j < U; ++j)
             if (t0 + j * 1024 < m) dst[t0 + j * 1024] = x[j];
     }
-    __syncthreads();                         // every wavefront has waited for its stores
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
     if (threadIdx.x == 0) {
-        __threadfence_system();
-        __hip_atomic_store(done, number, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "");    // system scope: the write-back, and a wait for it
+        __hip_atomic_store(done, number, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     }
 }
 

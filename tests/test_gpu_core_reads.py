@@ -1,0 +1,76 @@
+"""tt_cross_get_cores into device memory, bit for bit the host read: by one
+workgroup's copy kernel up to 32768 doubles, by a copy command above, read
+by another stream as soon as the call returns."""
+import ctypes as C
+
+import numpy as np
+import pytest
+
+from paper_2407_11290_amd import FN_SEPSUM, PREC_FP64, _lib
+from paper_2407_11290_amd.api import TTCross, batch_run
+
+pytestmark = pytest.mark.gpu
+
+GUARD = 64
+
+
+def _say(*a):
+    print("[case]", *a, flush=True)
+
+
+def _solved(n, r, stream=None, seed=1):
+    rng = np.random.default_rng(seed)
+    params = np.concatenate([[float(r)], 0.5 + rng.random(r * int(np.sum(n)))])
+    p = TTCross(n, 1e-13, FN_SEPSUM, params, seed=1, precision=PREC_FP64, stream=stream)
+    p.run()
+    assert int(max(p.ranks())) == r
+    return p
+
+
+def _read(p, buf, off):
+    """Length of the cores, copied to the GPU buffer buf from entry off on."""
+    return _lib.check(_lib.load().tt_cross_get_cores(p.h, C.c_void_p(buf.data_ptr() + 8 * off), buf.numel() - off, 1))
+
+
+# lengths r (n_1 + n_2): one pass of a thread, whole rounds of 8192 and one more or less, both sides of the switch
+CASES = [([3, 4], 1), ([500, 523], 1), ([512, 513], 1), ([60, 964], 8), ([100, 924], 8), ([1023, 3073], 2),
+         ([64, 16319], 2), ([64, 16320], 2), ([64, 16321], 2), ([700, 2600], 12)]
+
+
+@pytest.mark.parametrize("n,r", CASES)
+@pytest.mark.parametrize("own", [True, False])
+def test_device_read_is_complete_when_it_returns(n, r, own):
+    import torch
+    _say("device read", n, r, "own stream" if own else "caller's stream")
+    s = None if own else torch.cuda.Stream()
+    other = torch.cuda.Stream()
+    p = _solved(n, r, None if own else s.cuda_stream)
+    want = p.cores_flat()
+    m = want.size
+    assert m == r * sum(n)
+    for k in range(20):
+        buf = torch.full((m + 2 * GUARD,), float("nan"), dtype=torch.float64, device="cuda")
+        torch.cuda.synchronize()
+        assert _read(p, buf, GUARD) == m
+        with torch.cuda.stream(other):
+            got = buf.clone()
+        other.synchronize()
+        got = got.cpu().numpy()
+        assert np.array_equal(got[GUARD:GUARD + m].view(np.uint64), want.view(np.uint64)), k
+        assert np.isnan(got[:GUARD]).all() and np.isnan(got[GUARD + m:]).all(), k
+
+
+def test_device_reads_after_a_batch():
+    """As a program collects a batch: every problem's cores, one after the
+    other, into one buffer."""
+    import torch
+    ps = [_solved([20 + 3 * i, 30 + i], 1 + i % 9, seed=i) for i in range(60)]
+    want = np.concatenate([p.cores_flat() for p in ps])
+    batch_run(ps)
+    buf = torch.zeros(want.size, dtype=torch.float64, device="cuda")
+    torch.cuda.synchronize()
+    off = 0
+    for p in ps:
+        off += _read(p, buf, off)
+    assert off == want.size
+    assert np.array_equal(buf.cpu().numpy().view(np.uint64), want.view(np.uint64))
