@@ -307,7 +307,6 @@ int Problem::allocate()
     }
     if ((st = upload_fn(fn)) != TT_OK) return st;
     {
-        int dev = 0;
         HIPCHK(hipGetDevice(&dev));
         HIPCHK(hipDeviceGetAttribute(&lds_limit, hipDeviceAttributeMaxSharedMemoryPerBlock, dev));
         // the search kernels' static LDS comes off the top: a fixed reserve, so
@@ -1302,11 +1301,15 @@ struct DoneSlot {
     }
 };
 
-// The calling thread's flag; stream: replaced by the shared one if it is a
-// handle's own and on the same device.
-static bool done_slot(int **flag, int **dflag, bool own, hipStream_t *stream)
+// The calling thread's flag for a copy of a handle on device hdev; stream:
+// replaced by the shared one if it is the handle's own.  False where a kernel
+// would run on another device than the handle's: if another is current, or
+// the shared stream is another's.
+static bool done_slot(int **flag, int **dflag, int hdev, bool own, hipStream_t *stream)
 {
     static thread_local DoneSlot slot;
+    int dev = -1;
+    if (hipGetDevice(&dev) != hipSuccess || dev != hdev) return false;
     std::lock_guard<std::mutex> lk(g_done_mu);
     if (!g_done_page) {
         void *h = nullptr, *d = nullptr;
@@ -1321,8 +1324,8 @@ static bool done_slot(int **flag, int **dflag, bool own, hipStream_t *stream)
             return false;
         }
         std::memset(h, 0, sizeof(int) * kDoneSlots);
-        if (hipGetDevice(&g_done_device) != hipSuccess ||
-            hipStreamCreateWithFlags(&g_done_stream, hipStreamNonBlocking) != hipSuccess) {
+        g_done_device = dev;
+        if (hipStreamCreateWithFlags(&g_done_stream, hipStreamNonBlocking) != hipSuccess) {
             (void)hipGetLastError();
             (void)hipHostFree(h);
             g_done_stream = nullptr;
@@ -1336,8 +1339,7 @@ static bool done_slot(int **flag, int **dflag, bool own, hipStream_t *stream)
             g_done_used[i] = true;
             slot.at = i;
         }
-    int dev = -1;
-    if (slot.at < 0 || hipGetDevice(&dev) != hipSuccess || (own && dev != g_done_device)) return false;
+    if (slot.at < 0 || (own && dev != g_done_device)) return false;
     if (own) *stream = g_done_stream;
     *flag = g_done_page + slot.at;
     *dflag = g_done_dev + slot.at;
@@ -1620,7 +1622,7 @@ int64_t tt_cross_get_cores(tt_cross_h h, double *out, int64_t cap, int on_device
     if (cap < P.cores_len) return set_err(TT_EINVAL, "cap %lld < %lld", (long long)cap, (long long)P.cores_len);
     int *flag = nullptr, *dflag = nullptr;
     hipStream_t on = P.stream;
-    if (on_device && P.cores_len <= COPY_ONE && done_slot(&flag, &dflag, P.own_stream, &on)) {
+    if (on_device && P.cores_len <= COPY_ONE && done_slot(&flag, &dflag, P.dev, P.own_stream, &on)) {
         const int number = next_done_number();
         k_copy_one<<<1, 1024, 0, on>>>(P.d_cores, out, (int)P.cores_len, dflag, number);
         HIPCHK(hipGetLastError());

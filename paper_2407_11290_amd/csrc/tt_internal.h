@@ -62,6 +62,7 @@ struct Problem {
     hipStream_t stream = nullptr;
     bool own_stream = false;
     bool allocated = false;
+    int dev = -1;                  // device of the buffers
     int alloc_fp32 = -1, alloc_rmax = -1, alloc_tr = -1, alloc_tc = -1, alloc_ns = -1, alloc_pivot = -1,
         alloc_split = -1;
     int alloc_grid[TT_MAX_D] = {0};

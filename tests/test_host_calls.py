@@ -1,0 +1,107 @@
+"""What the library's calls ask of the HIP runtime, followed on the CPU: the
+built library runs against a host-only stand-in for the runtime
+(tests/hostrt/fake_hip.cpp), in a process of its own."""
+import os
+import subprocess
+import sys
+import textwrap
+
+import pytest
+
+from paper_2407_11290_amd import build
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+PRELUDE = """
+import ctypes as C, os, threading
+import numpy as np
+from paper_2407_11290_amd import _lib, FN_HILBERT, PREC_FP64, EDEVICE, EINVAL, ENOMEM
+from paper_2407_11290_amd.api import TTCross, default_options
+L = _lib.load()
+F = C.CDLL(os.environ["FAKE_HIP"])
+F.fake_malloc.restype = C.c_void_p
+F.fake_malloc.argtypes = [C.c_size_t, C.c_int]
+F.fake_limit.argtypes = [C.c_size_t]
+F.fake_in_use.restype = C.c_size_t
+HOOK = C.CFUNCTYPE(None, C.c_char_p, C.c_void_p)
+
+def lines(f):
+    b = C.create_string_buffer(1 << 20)
+    f(b, len(b))
+    return b.value.decode().splitlines()
+
+def faults():
+    return lines(F.fake_faults)
+
+def log(what=""):
+    return [x for x in lines(F.fake_log) if what in x]
+
+def solved(n=(6, 5, 7), stream=None):
+    p = TTCross(list(n), 1e-8, FN_HILBERT, precision=PREC_FP64, stream=stream)
+    assert p.run() == 0 and list(p.ranks()) == [1] * (len(n) + 1)
+    return p
+
+def read(p, ptr, cap=None):
+    m = int(sum(p.n))
+    got = L.tt_cross_get_cores(p.h, C.c_void_p(ptr), m if cap is None else cap, 1)
+    return got, np.ctypeslib.as_array((C.c_double * m).from_address(ptr)).copy()
+
+def sampled(p, R, seed=1):
+    e = C.c_double()
+    return L.tt_cross_sampled_error(p.h, R, C.c_uint64(seed), C.byref(e))
+"""
+
+
+@pytest.fixture(scope="session")
+def fake(tmp_path_factory):
+    """Runs code in a process of its own, on the stand-in runtime."""
+    lib = tmp_path_factory.mktemp("hostrt") / "libfakehip.so"
+    subprocess.run([build.HIPCC, "--offload-host-only", "-O1", "-std=c++17", "-shared", "-fPIC", "-w", "-I",
+                    os.path.join(ROOT, "include"), "-I", build.CSRC,
+                    os.path.join(ROOT, "tests", "hostrt", "fake_hip.cpp"), "-o", str(lib)], check=True)
+
+    def run(code):
+        env = dict(os.environ, LD_PRELOAD=str(lib), FAKE_HIP=str(lib), PYTHONPATH=ROOT)
+        env.pop("TT_CROSS_LIB", None)
+        r = subprocess.run([sys.executable, "-c", PRELUDE + textwrap.dedent(code)], env=env, cwd=ROOT, timeout=60,
+                           capture_output=True, text=True)
+        assert r.returncode == 0, r.stdout + r.stderr
+        return r.stdout
+    return run
+
+
+def test_core_read_goes_to_the_buffer(fake):
+    fake("""
+    p = solved()
+    m = sum(p.n)
+    buf = F.fake_malloc(8 * m, 0)
+    F.fake_clear()
+    got, x = read(p, buf)
+    assert got == m and list(x) == list(range(1, m + 1)), (got, x)
+    assert len(log("k_copy_one")) == 1 and not faults(), (log(), faults())
+    """)
+
+
+def test_core_read_runs_on_the_handles_device(fake):
+    """A handle made on one GPU and read while another is current: before, a
+    copy on the handle's own stream, and it may not become a kernel of the
+    other GPU, which has no access to the cores."""
+    fake("""
+    F.fake_set_device(0)
+    a = solved()
+    m = sum(a.n)
+    buf0 = F.fake_malloc(8 * m, 0)
+    assert read(a, buf0)[0] == m                 # the first read, on GPU 0
+    F.fake_set_device(1)
+    b = solved()
+    buf1 = F.fake_malloc(8 * m, 0)
+    for cur in (1, 0):
+        F.fake_set_device(cur)
+        F.fake_clear()
+        got, x = read(b, buf1)
+        assert got == m and list(x) == list(range(1, m + 1)), (cur, got, x)
+        assert not faults(), (cur, faults())
+    F.fake_set_device(1)
+    F.fake_clear()
+    assert read(a, buf0)[0] == m and not faults(), faults()
+    """)
