@@ -1355,6 +1355,24 @@ static int next_done_number()
     return (int)v;
 }
 
+// Whether a kernel of device dev may write n doubles at p: ordinary memory of
+// that device, all of it in p's allocation.  (A copy command looks at this
+// itself, and takes other memory its own way or refuses the range.)
+static bool kernel_target(const double *p, int64_t n, int dev)
+{
+    if ((uintptr_t)p & 7) return false;
+    hipPointerAttribute_t at;
+    hipDeviceptr_t base = nullptr;
+    size_t size = 0;
+    if (hipPointerGetAttributes(&at, p) != hipSuccess ||
+        hipMemGetAddressRange(&base, &size, (hipDeviceptr_t)const_cast<double *>(p)) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return at.type == hipMemoryTypeDevice && at.device == dev &&
+           (size_t)((const char *)p - (const char *)base) + sizeof(double) * (size_t)n <= size;
+}
+
 static void free_done_page()                    // no handle is left
 {
     std::lock_guard<std::mutex> lk(g_done_mu);
@@ -1622,7 +1640,8 @@ int64_t tt_cross_get_cores(tt_cross_h h, double *out, int64_t cap, int on_device
     if (cap < P.cores_len) return set_err(TT_EINVAL, "cap %lld < %lld", (long long)cap, (long long)P.cores_len);
     int *flag = nullptr, *dflag = nullptr;
     hipStream_t on = P.stream;
-    if (on_device && P.cores_len <= COPY_ONE && done_slot(&flag, &dflag, P.dev, P.own_stream, &on)) {
+    if (on_device && P.cores_len <= COPY_ONE && kernel_target(out, P.cores_len, P.dev) &&
+        done_slot(&flag, &dflag, P.dev, P.own_stream, &on)) {
         const int number = next_done_number();
         k_copy_one<<<1, 1024, 0, on>>>(P.d_cores, out, (int)P.cores_len, dflag, number);
         HIPCHK(hipGetLastError());

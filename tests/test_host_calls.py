@@ -105,3 +105,32 @@ def test_core_read_runs_on_the_handles_device(fake):
     F.fake_clear()
     assert read(a, buf0)[0] == m and not faults(), faults()
     """)
+
+
+@pytest.mark.parametrize("target", ["host", "pinned", "peer", "short", "misaligned"])
+def test_core_read_into_other_memory(fake, target):
+    """Targets that a copy command takes or refuses by itself go to it, as
+    before: pageable and pinned host memory, another GPU's memory, a range
+    past its allocation (an error), an address between two doubles."""
+    fake(f"""
+    target = {target!r}
+    p = solved()
+    m = sum(p.n)
+    if target == "host":
+        room = (C.c_char * (8 * m + 64))()
+        ptr = C.addressof(room)
+    elif target == "peer":
+        F.fake_set_device(1)
+        ptr = F.fake_malloc(8 * m, 0)
+        F.fake_set_device(0)
+    else:
+        ptr = F.fake_malloc(8 * m + 16, int(target == "pinned"))
+        ptr += {{"pinned": 0, "short": 24, "misaligned": 4}}[target]
+    F.fake_clear()
+    got, x = read(p, ptr)
+    assert not faults() and not log("k_copy_one") and len(log("hipMemcpyAsync %d " % (8 * m))) == 1, (faults(), log())
+    if target == "short":
+        assert got == EDEVICE, got
+    else:
+        assert got == m and list(x) == list(range(1, m + 1)), (got, x)
+    """)
