@@ -1278,13 +1278,16 @@ static std::mutex g_err_mu;
 static unsigned char *g_err_ws = nullptr;
 static size_t g_err_bytes = 0;
 static int g_err_dev = -1;
-static std::atomic<int> g_handles{0};
 
 // Flags in one page of mapped host memory, one per host thread: a short kernel
 // writes its number there when it is done.  (One page for all: a page of each
 // handle's costs the device an address translation per copy, 8 us.)  The page
-// goes with the last handle; a thread past the last flag gets none.
+// and its stream go with the last handle: only calls on handles use them, and
+// handles are counted under the page's lock, so that at a count of zero nobody
+// does, and a handle made later finds them whole or makes its own.  A thread
+// past the last flag gets none.
 static std::mutex g_done_mu;
+static int64_t g_handles = 0;
 static int *g_done_page = nullptr, *g_done_dev = nullptr;
 static hipStream_t g_done_stream = nullptr;
 static int g_done_device = -1;
@@ -1373,13 +1376,28 @@ static bool kernel_target(const double *p, int64_t n, int dev)
            (size_t)((const char *)p - (const char *)base) + sizeof(double) * (size_t)n <= size;
 }
 
-static void free_done_page()                    // no handle is left
+static void handle_made()
 {
     std::lock_guard<std::mutex> lk(g_done_mu);
-    if (g_done_stream) (void)hipStreamDestroy(g_done_stream);
-    g_done_stream = nullptr;
-    if (g_done_page) (void)hipHostFree(g_done_page);
-    g_done_page = g_done_dev = nullptr;
+    ++g_handles;
+}
+
+// True for the last handle, whose page and stream are given back.
+static bool handle_gone()
+{
+    int *page;
+    hipStream_t stream;
+    {
+        std::lock_guard<std::mutex> lk(g_done_mu);
+        if (--g_handles != 0) return false;
+        page = g_done_page;
+        stream = g_done_stream;
+        g_done_page = g_done_dev = nullptr;
+        g_done_stream = nullptr;
+    }
+    if (stream) (void)hipStreamDestroy(stream);
+    if (page) (void)hipHostFree(page);
+    return true;
 }
 
 static void free_err_ws()                       // with the lock held
@@ -1507,7 +1525,7 @@ tt_cross_h tt_cross_create(int d, const int32_t *n, double eps, int fn_id, const
     for (int j = 0; j < d; ++j) P.n[j] = n[j];
     P.eps = eps;
     tt_options_default(&P.opt);
-    g_handles.fetch_add(1);
+    handle_made();
     return h;
 }
 
@@ -1986,12 +2004,10 @@ void tt_cross_destroy(tt_cross_h h)
     // a run in flight is finished first: its kernels use the buffers
     if (h->p.busy()) (void)h->p.advance(true);
     delete h;
-    if (g_handles.fetch_sub(1) == 1) {
+    if (handle_gone()) {
+        // (a check of a handle made meanwhile holds the lock while it uses it)
         std::lock_guard<std::mutex> lk(g_err_mu);
-        if (g_handles.load() == 0) {
-            free_err_ws();
-            free_done_page();
-        }
+        free_err_ws();
     }
 }
 

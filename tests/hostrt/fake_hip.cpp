@@ -33,6 +33,7 @@ std::vector<std::string> log_, faults;
 std::map<std::string, int> fail_at;              // calls left until the call of that name fails
 size_t in_use = 0, limit = ~(size_t)0;
 thread_local int cur = 0;
+thread_local hipError_t last = hipSuccess;
 void (*hook)(const char *, const void *) = nullptr;
 struct Config { dim3 g, b; size_t lds; hipStream_t s; };
 thread_local std::vector<Config> configs;
@@ -106,7 +107,7 @@ hipError_t release(void *p, const char *who)
 hipError_t launch(const void *fn, dim3 grid, void **args, hipStream_t s)
 {
     std::string name = names.count(fn) ? names[fn] : "?";
-    if (fails("hipLaunchKernel", name.c_str())) return hipErrorLaunchFailure;
+    if (fails("hipLaunchKernel", name.c_str())) return last = hipErrorLaunchFailure;
     const int dev = stream_dev(s, "launch");
     char line[256];
     snprintf(line, sizeof line, "launch %.60s dev %d stream %p grid %u", name.c_str(), dev, (void *)s, grid.x);
@@ -201,7 +202,7 @@ void __hipRegisterVar(void **, void *, char *, char *, int, size_t, int, int) {}
 hipError_t hipGetDevice(int *d) { *d = cur; return hipSuccess; }
 hipError_t hipDeviceGetAttribute(int *v, hipDeviceAttribute_t, int) { *v = 163840; return hipSuccess; }
 hipError_t hipFuncGetAttributes(hipFuncAttributes *a, const void *) { memset(a, 0, sizeof *a); return hipSuccess; }
-hipError_t hipGetLastError() { return hipSuccess; }
+hipError_t hipGetLastError() { const hipError_t e = last; last = hipSuccess; return e; }
 const char *hipGetErrorString(hipError_t e) { return e == hipSuccess ? "no error" : e == hipErrorOutOfMemory ? "out of memory" : "error"; }
 hipError_t hipGetSymbolAddress(void **p, const void *) { return alloc(p, 16 << 20, false); }
 

@@ -74,3 +74,57 @@ def test_device_reads_after_a_batch():
         off += _read(p, buf, off)
     assert off == want.size
     assert np.array_equal(buf.cpu().numpy().view(np.uint64), want.view(np.uint64))
+
+
+def _in_threads(n, work):
+    import threading
+    errs = []
+
+    def body(i):
+        try:
+            work(i)
+        except BaseException as e:                   # (an assertion in a thread would be lost)
+            errs.append((i, repr(e)))
+
+    ts = [threading.Thread(target=body, args=(i,)) for i in range(n)]
+    for t in ts:
+        t.start()
+    for t in ts:
+        t.join()
+    assert not errs, errs
+
+
+def test_threads_read_the_cores_of_their_own_handles():
+    import torch
+    ps = [_solved([50 + 40 * i, 70], 1 + i, seed=i) for i in range(8)]
+    want = [p.cores_flat() for p in ps]
+    bufs = [torch.zeros(w.size, dtype=torch.float64, device="cuda") for w in want]
+    torch.cuda.synchronize()
+    _say("threads")
+
+    def work(i):
+        for _ in range(200):
+            assert _read(ps[i], bufs[i], 0) == want[i].size
+
+    _in_threads(len(ps), work)
+    for b, w in zip(bufs, want):
+        assert np.array_equal(b.cpu().numpy().view(np.uint64), w.view(np.uint64))
+
+
+def test_last_handles_come_and_go_in_two_threads():
+    """Handles are made, solved, read, checked and destroyed in two threads,
+    so that the last one goes while the other thread makes or reads its own."""
+    import torch
+    bufs = [torch.zeros(9 * 60, dtype=torch.float64, device="cuda") for _ in range(2)]
+    torch.cuda.synchronize()
+
+    def work(i):
+        for k in range(30):
+            _say("thread", i, "handle", k)
+            p = _solved([20 + i, 40 - i], 3 + k % 7, seed=k)
+            m = _read(p, bufs[i], 0)
+            assert np.array_equal(bufs[i].cpu().numpy()[:m].view(np.uint64), p.cores_flat().view(np.uint64))
+            assert p.sampled_error(500 + k, 3) < 1e-9
+            p.close()
+
+    _in_threads(2, work)

@@ -134,3 +134,87 @@ def test_core_read_into_other_memory(fake, target):
     else:
         assert got == m and list(x) == list(range(1, m + 1)), (got, x)
     """)
+
+
+def test_last_handle_destroyed_beside_a_new_ones_core_read(fake):
+    """One thread destroys the last handle and is stopped while the check's
+    workspace is given back; another makes a handle, solves, and is stopped
+    as its core copy is launched; the first goes on.  What the copy uses (its
+    flag, its stream) must still be there."""
+    fake("""
+    a = solved()
+    m = sum(a.n)
+    buf = F.fake_malloc(8 * m, 0)
+    assert read(a, buf)[0] == m                  # the flag page and its stream are there
+    F.fake_clear()
+    assert sampled(a, 1000) >= 0                 # and the workspace
+    size = int(log("hipMalloc")[-1].split()[1])
+    launched, destroyed = threading.Event(), threading.Event()
+    made, state, result = [], {"at": None}, []
+
+    def second():
+        p = solved()
+        made.append(p)
+        result.append(read(p, buf))
+
+    def hook(name, arg):
+        me = threading.current_thread()
+        if me is first and name == b"hipFree" and a.h is None and not made:
+            # the handle's own buffers go first; the workspace is the last
+            pending["frees"] += 1
+            if pending["frees"] == pending["stop_at"]:
+                t2.start()
+                assert launched.wait(30)
+        if me is t2 and name == b"hipLaunchKernel" and b"k_copy_one" in C.string_at(arg):
+            launched.set()
+            assert destroyed.wait(30)
+
+    def destroy(p):
+        h, p.h = p.h, None
+        L.tt_cross_destroy(C.c_void_p(h))
+
+    # how many frees a destroyed last handle makes, the workspace's included
+    pending = {"frees": 0, "stop_at": -1}
+    first = threading.current_thread()
+    t2 = threading.Thread(target=second)
+    cb = HOOK(hook)
+    F.fake_hook(cb)
+    destroy(a)
+    F.fake_hook(HOOK())
+    total = pending["frees"]
+    for stop_at in range(1, total + 1):
+        a = solved()
+        assert read(a, buf)[0] == m and sampled(a, 1000) >= 0
+        made.clear(); result.clear(); launched.clear(); destroyed.clear()
+        pending = {"frees": 0, "stop_at": stop_at}
+        t2 = threading.Thread(target=second)
+        F.fake_clear()
+        F.fake_hook(cb)
+        destroy(a)
+        destroyed.set()
+        t2.join()
+        F.fake_hook(HOOK())
+        assert not faults(), (stop_at, total, faults())
+        got, x = result[0]
+        assert got == m and list(x) == list(range(1, m + 1)), (stop_at, got)
+        made[0].close()
+    """)
+
+
+def test_everything_is_given_back_with_the_last_handle(fake):
+    fake("""
+    for rep in range(3):
+        ps = [solved() for _ in range(3)]
+        m = sum(ps[0].n)
+        buf = F.fake_malloc(8 * m, 0)
+        for p in ps:
+            assert read(p, buf)[0] == m and sampled(p, 1000) >= 0
+        before = F.fake_in_use()
+        for p in ps:
+            p.close()
+        left = F.fake_in_use()
+        if rep == 0:
+            base = left
+        assert left == base + 8 * m * rep and before > left, (rep, left, base)
+        assert not faults(), faults()
+    """)
