@@ -1424,7 +1424,11 @@ static int sampled_error_on(Problem &P, int64_t R, uint64_t seed, const ErrBufs 
     double hp[2 * kErrParts];
     if (e == hipSuccess) e = hipMemcpyAsync(hp, b.part, sizeof hp, hipMemcpyDeviceToHost, P.stream);
     if (e == hipSuccess) e = hipStreamSynchronize(P.stream);
-    if (e != hipSuccess) return set_err(TT_EDEVICE, "sampled error: %s", hipGetErrorString(e));
+    if (e != hipSuccess) {
+        // nothing queued may still use the buffers: the next check gets them
+        (void)hipStreamSynchronize(P.stream);
+        return set_err(TT_EDEVICE, "sampled error: %s", hipGetErrorString(e));
+    }
     double num = 0, den = 0;
     for (int i = 0; i < kErrParts; ++i) { num += hp[2 * i]; den += hp[2 * i + 1]; }
     *err = den > 0 ? std::sqrt(num / den) : std::sqrt(num);

@@ -218,3 +218,22 @@ def test_everything_is_given_back_with_the_last_handle(fake):
         assert left == base + 8 * m * rep and before > left, (rep, left, base)
         assert not faults(), faults()
     """)
+
+
+@pytest.mark.parametrize("name,nth", [("hipMemcpyAsync", 1), ("hipLaunchKernel", 2), ("hipLaunchKernel", 4)])
+def test_failed_check_leaves_nothing_queued_on_the_kept_workspace(fake, name, nth):
+    """A check that fails on the way has kernels queued that write the
+    workspace; the next check, on another stream, gets the same memory, so
+    the failed one waits for its stream before it returns."""
+    fake(f"""
+    p = solved()
+    assert sampled(p, 1000) >= 0
+    F.fake_clear()
+    F.fake_fail({name.encode()!r}, {nth})
+    assert sampled(p, 1000) == EDEVICE
+    calls = log()
+    stream = [x for x in calls if x.startswith("launch")][0].split("stream ")[1].split()[0]
+    last = max(i for i, x in enumerate(calls) if x.startswith("launch"))
+    assert any(x == "hipStreamSynchronize " + stream for x in calls[last + 1:]), calls
+    assert sampled(p, 1000) >= 0 and not faults()
+    """)
