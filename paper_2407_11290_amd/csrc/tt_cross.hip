@@ -1807,6 +1807,9 @@ int tt_cross_sampled_error(tt_cross_h h, int64_t R, uint64_t seed, double *err)
     Problem &P = h->p;
     if (!P.ran) return set_err(TT_ESTATE, "no completed run");
     if (R < 1) return set_err(TT_EINVAL, "R must be >= 1");
+    // (a size past what can be addressed may not wrap around to a small one)
+    if ((uint64_t)R > (SIZE_MAX >> 1) / (sizeof(int) * P.d + 2 * sizeof(double)))
+        return set_err(TT_ENOMEM, "sampled error: no memory for %lld samples", (long long)R);
     const size_t bi = kScrAlign(sizeof(int) * (size_t)R * P.d), bx = kScrAlign(sizeof(double) * (size_t)R),
                  need = bi + 2 * bx + sizeof(double) * 2 * kErrParts;
     // the workspace kept between checks, if it can hold this one and no other

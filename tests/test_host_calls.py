@@ -237,3 +237,17 @@ def test_failed_check_leaves_nothing_queued_on_the_kept_workspace(fake, name, nt
     assert any(x == "hipStreamSynchronize " + stream for x in calls[last + 1:]), calls
     assert sampled(p, 1000) >= 0 and not faults()
     """)
+
+
+@pytest.mark.parametrize("R", [-(-2**64 // 28), -(-2**64 // 28) + 100, 2**62, 2**63 - 1])
+def test_check_of_too_many_samples_is_refused(fake, R):
+    """Sample counts whose buffers pass what an address can hold: refused
+    before anything is launched (one buffer's size may not wrap around to a
+    small one)."""
+    fake(f"""
+    p = solved()
+    F.fake_clear()
+    assert sampled(p, {R}) == ENOMEM, _lib.last_error()
+    assert not log("launch") and not faults(), (log(), faults())
+    assert sampled(p, 1000) >= 0
+    """)
