@@ -1892,8 +1892,10 @@ struct EvalEntry {
 std::mutex g_eval_mu;
 std::vector<std::unique_ptr<EvalEntry>> g_eval_cache;
 uint64_t g_eval_clock = 0;
-hipEvent_t g_eval_ev[2] = {nullptr, nullptr};   // attached to the last evaluation's dispatch
-bool g_eval_done = false;
+// events attached to the dispatches of the last evaluation that completed
+// (pair g_eval_done; -1: none) and of the next one, which may fail
+hipEvent_t g_eval_ev[2][2] = {{nullptr, nullptr}, {nullptr, nullptr}};
+int g_eval_done = -1;
 }  // namespace
 
 // Bulk evaluation behind tt_fn_eval (V = double) and tt_fn_eval_f32.
@@ -1966,11 +1968,12 @@ static int fn_eval_impl(int fn_id, int d, const int32_t *n, const double *params
         didx = (const int *)ti;
         dout = (V *)to;
     }
-    for (hipEvent_t &ev : g_eval_ev)
+    const int pair = g_eval_done == 0 ? 1 : 0;
+    for (hipEvent_t &ev : g_eval_ev[pair])
         if (e == hipSuccess && !ev) e = hipEventCreate(&ev);
-    if (e == hipSuccess) e = launch_fn_eval<V>(fh.dev, m, didx, dout, nullptr, g_eval_ev[0], g_eval_ev[1]);
+    if (e == hipSuccess) e = launch_fn_eval<V>(fh.dev, m, didx, dout, nullptr, g_eval_ev[pair][0], g_eval_ev[pair][1]);
     if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
-    if (e == hipSuccess) g_eval_done = true;    // its time is read when it is asked for
+    if (e == hipSuccess) g_eval_done = pair;    // its time is read when it is asked for
     if (e == hipSuccess && !on_device) e = hipMemcpy(out, dout, sizeof(V) * m, hipMemcpyDeviceToHost);
     if (ti) (void)hipFree(ti);
     if (to) (void)hipFree(to);
@@ -1998,9 +2001,9 @@ int tt_fn_eval_last_kernel_ms(double *ms)
 {
     if (!ms) return set_err(TT_EINVAL, "ms is NULL");
     std::lock_guard<std::mutex> lk(g_eval_mu);
-    if (!g_eval_done) return set_err(TT_ESTATE, "no bulk evaluation has completed");
+    if (g_eval_done < 0) return set_err(TT_ESTATE, "no bulk evaluation has completed");
     float t = 0.0f;
-    HIPCHK(hipEventElapsedTime(&t, g_eval_ev[0], g_eval_ev[1]));
+    HIPCHK(hipEventElapsedTime(&t, g_eval_ev[g_eval_done][0], g_eval_ev[g_eval_done][1]));
     *ms = t;
     return TT_OK;
 }

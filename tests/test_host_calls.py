@@ -15,7 +15,7 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 PRELUDE = """
 import ctypes as C, os, threading
 import numpy as np
-from paper_2407_11290_amd import _lib, FN_HILBERT, PREC_FP64, EDEVICE, EINVAL, ENOMEM
+from paper_2407_11290_amd import _lib, FN_HILBERT, PREC_FP64, EDEVICE, EINVAL, ENOMEM, ESTATE
 from paper_2407_11290_amd.api import TTCross, default_options
 L = _lib.load()
 F = C.CDLL(os.environ["FAKE_HIP"])
@@ -250,4 +250,30 @@ def test_check_of_too_many_samples_is_refused(fake, R):
     assert sampled(p, {R}) == ENOMEM, _lib.last_error()
     assert not log("launch") and not faults(), (log(), faults())
     assert sampled(p, 1000) >= 0
+    """)
+
+
+def test_time_of_the_last_bulk_evaluation_that_completed(fake):
+    """A later evaluation that fails does not count."""
+    fake("""
+    n = np.array([9, 9, 9], dtype=np.int32)
+
+    def evaluate(m):
+        idx = np.zeros((m, 3), dtype=np.int32)
+        out = np.zeros(m)
+        return L.tt_fn_eval(FN_HILBERT, 3, n.ctypes.data_as(C.POINTER(C.c_int32)), None, 0, m, idx.ctypes.data_as(C.c_void_p),
+                            out.ctypes.data_as(C.c_void_p), 0)
+
+    ms = C.c_double()
+    assert L.tt_fn_eval_last_kernel_ms(C.byref(ms)) == ESTATE
+    F.fake_fail(b"hipStreamSynchronize", 1)
+    assert evaluate(5000) == EDEVICE
+    assert L.tt_fn_eval_last_kernel_ms(C.byref(ms)) == ESTATE
+    for m, want in ((5000, 4.0), (20000, 15.0), (1000, 1.0)):
+        assert evaluate(m) == 0 and L.tt_fn_eval_last_kernel_ms(C.byref(ms)) == 0 and ms.value == want, (m, ms.value)
+        for name, nth in ((b"hipStreamSynchronize", 1), (b"hipLaunchKernel", 1)):
+            F.fake_fail(name, nth)
+            assert evaluate(100000) == EDEVICE
+            ms.value = -1.0
+            assert L.tt_fn_eval_last_kernel_ms(C.byref(ms)) == 0 and ms.value == want, (m, name, ms.value)
     """)
