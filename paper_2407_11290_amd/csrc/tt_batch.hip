@@ -65,10 +65,10 @@ int Engine::init(int capacity, hipStream_t s)
     if (capacity < 1 || capacity > 65535) return set_err(TT_EINVAL, "engine capacity %d outside [1,65535]", capacity);
     stream = s;
     cap = capacity;
-    HIPCHK(hipMalloc(&dPa, sizeof(ProbDev) * cap));
+    HIPCHK(dev_malloc((void **)&dPa, sizeof(ProbDev) * cap));
     shadow.assign(cap, ProbDev{});
     shadow_ok.assign(cap, 0);
-    HIPCHK(hipMalloc(&dS, sizeof(ProbState) * cap));
+    HIPCHK(dev_malloc((void **)&dS, sizeof(ProbState) * cap));
     HIPCHK(hipHostMalloc((void **)&hPa, sizeof(ProbDev) * cap, hipHostMallocDefault));
     // finished states and check partials are written by kernels straight
     // into mapped host memory (no copy per problem)

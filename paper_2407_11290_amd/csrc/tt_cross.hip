@@ -39,6 +39,43 @@ int set_err(int code, const char *fmt, ...)
 
 
 // ---------------------------------------------------------------------------
+// Device memory.
+// ---------------------------------------------------------------------------
+// One workspace of sampled-error checks is kept between calls (making and
+// freeing four buffers took 60 us of a million-sample check's 165), at most
+// kErrKeep bytes, until the last handle is destroyed or an allocation of the
+// library needs the room.  A call uses it under the lock and has waited for
+// its stream when it returns.
+constexpr size_t kErrKeep = (size_t)64 << 20;
+static std::mutex g_err_mu;
+static unsigned char *g_err_ws = nullptr;
+static size_t g_err_bytes = 0;
+static int g_err_dev = -1;
+
+static void free_err_ws()                       // with the lock held
+{
+    if (g_err_ws) (void)hipFree(g_err_ws);
+    g_err_ws = nullptr;
+    g_err_bytes = 0;
+}
+
+// hipMalloc; where there is no room, again without the kept workspace (if no
+// check is using it).
+hipError_t dev_malloc(void **p, size_t bytes)
+{
+    hipError_t e = hipMalloc(p, bytes);
+    if (e == hipErrorOutOfMemory) {
+        std::unique_lock<std::mutex> lk(g_err_mu, std::try_to_lock);
+        if (lk.owns_lock() && g_err_ws) {
+            (void)hipGetLastError();
+            free_err_ws();
+            e = hipMalloc(p, bytes);
+        }
+    }
+    return e;
+}
+
+// ---------------------------------------------------------------------------
 // Generating function descriptors.
 // ---------------------------------------------------------------------------
 // Per-mode tables of the Maxwellians.  Every value is the FP64 result of the
@@ -204,8 +241,8 @@ int upload_fn(FnHost &fh, hipStream_t stream)
         // a larger table: the old buffers may still be read by queued work
         if (stream) HIPCHK(hipStreamSynchronize(stream));
         fh.free_device();
-        HIPCHK(hipMalloc(&fh.d_table, m * sizeof(double)));
-        HIPCHK(hipMalloc(&fh.d_table32, m * sizeof(float)));
+        HIPCHK(dev_malloc((void **)&fh.d_table, m * sizeof(double)));
+        HIPCHK(dev_malloc((void **)&fh.d_table32, m * sizeof(float)));
         fh.d_cap = m;
     }
     if (stream) {
@@ -270,7 +307,7 @@ int Problem::dalloc(void **p, size_t bytes)
 {
     *p = nullptr;
     if (bytes == 0) bytes = 16;
-    hipError_t e = hipMalloc(p, bytes);
+    hipError_t e = dev_malloc(p, bytes);
     if (e != hipSuccess) {
         *p = nullptr;
         (void)hipGetLastError();
@@ -1269,16 +1306,6 @@ struct ErrBufs {
     double *part = nullptr;         // 2 kErrParts partial sums
 };
 
-// One workspace of sampled-error checks is kept between calls (making and
-// freeing four buffers took 60 us of a million-sample check's 165), at most
-// kErrKeep bytes, until the last handle is destroyed.  A call uses it under
-// the lock and has waited for its stream when it returns.
-constexpr size_t kErrKeep = (size_t)64 << 20;
-static std::mutex g_err_mu;
-static unsigned char *g_err_ws = nullptr;
-static size_t g_err_bytes = 0;
-static int g_err_dev = -1;
-
 // Flags in one page of mapped host memory, one per host thread: a short kernel
 // writes its number there when it is done.  (One page for all: a page of each
 // handle's costs the device an address translation per copy, 8 us.)  The page
@@ -1398,13 +1425,6 @@ static bool handle_gone()
     if (stream) (void)hipStreamDestroy(stream);
     if (page) (void)hipHostFree(page);
     return true;
-}
-
-static void free_err_ws()                       // with the lock held
-{
-    if (g_err_ws) (void)hipFree(g_err_ws);
-    g_err_ws = nullptr;
-    g_err_bytes = 0;
 }
 
 static int sampled_error_on(Problem &P, int64_t R, uint64_t seed, const ErrBufs &b, double *err)
@@ -1703,8 +1723,8 @@ int tt_eval(tt_cross_h h, int64_t m, const int32_t *idx, double *out, int on_dev
             for (int j = 0; j < P.d; ++j)
                 if (idx[t * P.d + j] < 0 || idx[t * P.d + j] >= P.n[j])
                     return set_err(TT_EINVAL, "index %lld,%d out of range", (long long)t, j);
-        HIPCHK(hipMalloc(&tmp_i, sizeof(int) * m * P.d));
-        HIPCHK(hipMalloc(&tmp_o, sizeof(double) * m));
+        HIPCHK(dev_malloc(&tmp_i, sizeof(int) * m * P.d));
+        HIPCHK(dev_malloc(&tmp_o, sizeof(double) * m));
         HIPCHK(hipMemcpyAsync(tmp_i, idx, sizeof(int) * m * P.d, hipMemcpyHostToDevice, P.stream));
         didx = (const int *)tmp_i;
         dout = (double *)tmp_o;
@@ -1822,7 +1842,12 @@ int tt_cross_sampled_error(tt_cross_h h, int64_t R, uint64_t seed, double *err)
         base = g_err_ws;
     } else {
         if (keep) free_err_ws();
-        const hipError_t e = hipMalloc(&base, need);
+        hipError_t e = hipMalloc(&base, need);
+        if (e == hipErrorOutOfMemory && lk.owns_lock() && g_err_ws) {
+            (void)hipGetLastError();
+            free_err_ws();
+            e = hipMalloc(&base, need);
+        }
         if (e != hipSuccess) {
             (void)hipGetLastError();
             return set_err(TT_ENOMEM, "sampled error: %s", hipGetErrorString(e));
@@ -1962,8 +1987,8 @@ static int fn_eval_impl(int fn_id, int d, const int32_t *n, const double *params
     void *ti = nullptr, *to = nullptr;
     hipError_t e = hipSuccess;
     if (!on_device) {
-        e = hipMalloc(&ti, sizeof(int) * m * d);
-        if (e == hipSuccess) e = hipMalloc(&to, sizeof(V) * m);
+        e = dev_malloc(&ti, sizeof(int) * m * d);
+        if (e == hipSuccess) e = dev_malloc(&to, sizeof(V) * m);
         if (e == hipSuccess) e = hipMemcpy(ti, idx, sizeof(int) * m * d, hipMemcpyHostToDevice);
         didx = (const int *)ti;
         dout = (V *)to;

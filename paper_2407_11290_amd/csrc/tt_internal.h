@@ -12,6 +12,7 @@
 namespace ttc {
 
 int set_err(int code, const char *fmt, ...);
+hipError_t dev_malloc(void **p, size_t bytes);
 
 #define HIPCHK(expr)                                                                        \
     do {                                                                                    \

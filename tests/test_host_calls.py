@@ -277,3 +277,27 @@ def test_time_of_the_last_bulk_evaluation_that_completed(fake):
             ms.value = -1.0
             assert L.tt_fn_eval_last_kernel_ms(C.byref(ms)) == 0 and ms.value == want, (m, name, ms.value)
     """)
+
+
+def test_kept_workspace_makes_room_for_a_solve(fake):
+    """Memory that a solve needs and only the check's kept workspace holds."""
+    fake("""
+    p = solved()
+    q = TTCross([40, 50, 60], 1e-8, FN_HILBERT, precision=PREC_FP64)
+    before = F.fake_in_use()
+    assert q.run() == 0
+    need = F.fake_in_use() - before
+    q.close()
+    assert sampled(p, 2000000) >= 0              # 2.8e7 bytes
+    assert need < 2e7
+    F.fake_limit(need // 2)
+    q = TTCross([40, 50, 60], 1e-8, FN_HILBERT, precision=PREC_FP64)
+    assert q.run() == 0
+    # and a check too large to be kept gets the room of the kept one
+    F.fake_limit(0)
+    assert sampled(p, 2000000) >= 0
+    F.fake_limit(int(2.8e8))
+    assert sampled(p, 10500000) >= 0             # 2.94e8 bytes
+    F.fake_limit(0)
+    assert sampled(p, 1000) >= 0 and not faults(), faults()
+    """)
