@@ -3490,10 +3490,13 @@ static __global__ void __launch_bounds__(te_threads(RM)) k_tt_eval_sort(TTArgs a
     for (int64_t base = (int64_t)blockIdx.x * S; base < m; base += (int64_t)gridDim.x * S) {
         const int cnt = (int)min((int64_t)S, m - base);
         const int64_t row = (base + min(tid, cnt - 1)) * d;
-        int i = IX[row + 1];
+        // (an index outside its mode is read as the nearest inside: it counts
+        // into the sort, where it would disturb the chunk's other indices)
+        auto index = [&](int k) { return min(max(IX[row + k], 0), a.n[k] - 1); };
+        int i = index(1);
         __syncthreads();                         // the previous chunk's reads are done
         // mode 1: the row vector is G_1(i_1, :)
-        if (tid < S) key[tid] = IX[row];
+        if (tid < S) key[tid] = index(0);
         __syncthreads();
         {
             const int rb = a.ranks[1], bb = min(gl, rb - 1);
@@ -3509,7 +3512,7 @@ static __global__ void __launch_bounds__(te_threads(RM)) k_tt_eval_sort(TTArgs a
             const gptr_t<const double> Gk = Gg + a.goff[k];
             const int64_t sa = (int64_t)n * rb;
             const int ik = i;
-            i = IX[row + k + 1];                 // the next mode's, in flight meanwhile
+            i = index(k + 1);                    // the next mode's, in flight meanwhile
             if (n <= NBIN) {
                 // counting sort: bin sizes (the buffer was cleared during the
                 // last mode's steps), their prefix sums, the order
