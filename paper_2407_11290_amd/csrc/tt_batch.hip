@@ -342,11 +342,14 @@ int Engine::tick(std::vector<int> *completed)
         } else {
             any_sweeping = true;
             // the next round's shapes have at most the committed ranks plus one
-            // per queued round; its stored tiles, one round fewer
+            // per queued round; its stored tiles, one round fewer (with none
+            // queued, those of the last one: taken for the committed ranks
+            // themselves, the new tiles counted as none, and the launch had a
+            // few workgroups for all of them)
             for (int k = 1; k <= s.Q->d - 1; ++k) {
                 const int rc = __atomic_load_n(&h.r[k], __ATOMIC_RELAXED), q = s.launched - s.done;
                 s.rub[k] = std::min(s.Q->rc[k], rc + q);
-                s.rst[k] = std::min(s.Q->rc[k], rc + std::max(0, q - 1));
+                s.rst[k] = std::max(1, std::min(s.Q->rc[k], rc + q - 1));
             }
         }
     }

@@ -3,7 +3,9 @@
 // launch runs at once on the calling thread.  Kernels do nothing, but
 //   k_commit      ends the run at rank 1 (it writes the host mirror),
 //   k_cores       fills the cores with 1, 2, 3, ... and leaves a clean state,
-//   k_copy_one    copies and raises its flag.
+//   k_copy_one    copies and raises its flag,
+//   k_commit_b    lets every problem of the launch grow by one rank a sweep, to
+//                 fake_sweeps sweeps, and k_state_out_b leaves clean states.
 // So a test can follow which memory, stream and device a call uses, make a
 // runtime call fail, and stop one thread inside a call while another goes on.
 // Faults (a dead stream or freed memory used, memory of another device
@@ -35,6 +37,9 @@ size_t in_use = 0, limit = ~(size_t)0;
 thread_local int cur = 0;
 thread_local hipError_t last = hipSuccess;
 void (*hook)(const char *, const void *) = nullptr;
+// a batched launch's problems (as in tt_kernels.h)
+struct Batch { int na; int boff[513]; uint16_t p[512]; };
+int batch_sweeps = 1;
 struct Config { dim3 g, b; size_t lds; hipStream_t s; };
 thread_local std::vector<Config> configs;
 
@@ -119,6 +124,25 @@ hipError_t launch(const void *fn, dim3 grid, void **args, hipStream_t s)
         for (int k = 0; k <= P->d; ++k) hm->r[k] = 1;
         hm->stop = 1;
         hm->sweeps_done = ((const SweepArgs *)args[1])->sweep + 1;
+    } else if (name.find("k_commit_b") != std::string::npos) {
+        const ProbDev *Pa = *(const ProbDev **)args[0];
+        const Batch &bm = *(const Batch *)args[1];
+        for (int b = 0; b < bm.na; ++b) {
+            const ProbDev &P = Pa[bm.p[b]];
+            HostMirror *hm = P.hm;
+            if (hm->stop) continue;
+            ++hm->sweeps_done;
+            hm->r[0] = hm->r[P.d] = 1;
+            hm->stop = hm->sweeps_done >= batch_sweeps;
+            for (int k = 1; k < P.d; ++k) hm->r[k] = hm->sweeps_done + (hm->stop ? 0 : 1);
+        }
+    } else if (name.find("k_state_out_b") != std::string::npos) {
+        ProbState *hS = *(ProbState **)args[1];
+        const Batch &bo = *(const Batch *)args[2];
+        for (int b = 0; b < bo.na; ++b) {
+            memset(hS + bo.p[b], 0, sizeof *hS);
+            hS[bo.p[b]].sweeps = batch_sweeps;
+        }
     } else if (name.find("7k_cores") != std::string::npos) {
         const ProbDev *P = *(const ProbDev **)args[0];
         double *G = *(double **)args[2];
@@ -163,6 +187,7 @@ extern "C" {
 // --- for the tests ---------------------------------------------------------
 void fake_hook(void (*f)(const char *, const void *)) { hook = f; }
 void fake_set_device(int d) { cur = d; }
+void fake_sweeps(int n) { batch_sweeps = n; }
 void fake_limit(size_t bytes) { std::lock_guard<std::recursive_mutex> l(mu); limit = bytes ? in_use + bytes : ~(size_t)0; }
 void fake_fail(const char *name, int nth) { std::lock_guard<std::recursive_mutex> l(mu); fail_at[name] = nth; }
 size_t fake_in_use() { std::lock_guard<std::recursive_mutex> l(mu); return in_use; }

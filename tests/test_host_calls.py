@@ -301,3 +301,23 @@ def test_kept_workspace_makes_room_for_a_solve(fake):
     F.fake_limit(0)
     assert sampled(p, 1000) >= 0 and not faults(), faults()
     """)
+
+
+@pytest.mark.parametrize("count", [1, 3])
+def test_batched_sweeps_have_a_workgroup_per_new_tile(fake, count):
+    """The device finishes every round before the host looks: with no round
+    queued the next one still has the new tiles of the last commit (64 points
+    in two blocks: 2 x 2 tiles of a new prefix or suffix, two unfoldings)."""
+    fake(f"""
+    from paper_2407_11290_amd.api import batch_run
+    F.fake_sweeps(6)
+    ps = [TTCross([64] * 3, 1e-8, FN_HILBERT, precision=PREC_FP64, grid=[2] * 3, seed=i, lookahead=1)
+          for i in range({count})]
+    batch_run(ps[:1])                            # (buffers)
+    F.fake_clear()
+    batch_run(ps)
+    grids = [int(x.split("grid ")[1]) for x in log("k_sweep_b")]
+    assert len(grids) >= 6 and not faults(), (grids, faults())
+    assert all(g >= {count} * 8 for g in grids[2:6]), grids
+    assert all(list(p.ranks()) == [1, 6, 6, 1] for p in ps)
+    """)
