@@ -114,16 +114,6 @@ int Engine::admit(Problem *Q, void *user)
     Q->escalated = Q->force_fp64 ? 1 : 0;
     ProbDev &D = hPa[i];
     D = Q->hP;
-    // in a batch the chip is full: stored tiles are searched whole
-    for (int u = 0, acc = 0; u < Q->d - 1; ++u) {
-        KDev &K = D.kd[u];
-        K.smax = 0;
-        D.sh0.lsp[u] = 0;
-        D.sh0.soff[u] = acc;
-        D.sh0.ntl[u] = stored_tiles(K.nk, K.nk1, K.TR);
-        acc += D.sh0.ntl[u];
-        D.sh0.soff[u + 1] = acc;
-    }
     D.S = dS + i;
     D.hm = dhm + i;
     D.run.seed = Q->opt.seed;
@@ -166,6 +156,10 @@ int Engine::copy_slots(void *dst, const void *src, size_t elem, const std::vecto
 // Launch setup for every slot admitted since the last call.
 template <typename V> int Engine::launch_setup(std::vector<int> &ids)
 {
+    // the first sweeps' shapes; later ones follow the number of problems in
+    // their own launch
+    const int share = (int)std::min<size_t>(MAXB, ids.size());
+    for (int i : ids) first_shapes(hPa[i], share);
     // only descriptors that differ from what the device array already holds
     // are copied: a batch of the same problems run again copies none
     std::vector<int> changed;
@@ -224,7 +218,7 @@ template <typename V> int Engine::launch_sweep(std::vector<int> &ids)
                 const KDev &K = hPa[s.idx].kd[u];
                 int nnew, nst;
                 low = low && s.rub[k] <= 16;
-                sweep_units(K, s.rub, s.rst, k, d - 1, nnew, nst);
+                sweep_units(K, s.rub, s.rst, k, d - 1, na, nnew, nst);
                 tot += nnew + (nst + NT / 64 - 1) / (NT / 64);
                 lds = std::max(lds, sweep_lds_bytes(s.rub[k], K.TRn, K.TC, sizeof(V)));
             }

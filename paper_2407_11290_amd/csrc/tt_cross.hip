@@ -329,6 +329,25 @@ size_t Problem::device_bytes() const
     return tot;
 }
 
+// The first sweep searches the initial superblocks (one prefix, one suffix,
+// every tile stored): its tile counts are fixed by the geometry, and by the
+// number of problems whose sweeps share the launch.
+void first_shapes(ProbDev &H, int share)
+{
+    std::memset(&H.sh0, 0, sizeof H.sh0);
+    for (int u = 0, acc = 0; u < H.nk; ++u) {
+        const KDev &K = H.kd[u];
+        H.sh0.RT[u] = H.sh0.RTs[u] = K.RTn;
+        H.sh0.CT[u] = H.sh0.CTs[u] = K.CTq;
+        H.sh0.soff[u] = acc;
+        const int nst = stored_tiles(K.nk, K.nk1, K.TR);
+        H.sh0.lsp[u] = stored_split(nst, H.nk, share, K.smax);
+        H.sh0.ntl[u] = nst << H.sh0.lsp[u];
+        acc += H.sh0.ntl[u];
+        H.sh0.soff[u + 1] = acc;
+    }
+}
+
 int Problem::allocate()
 {
     if (allocated) return TT_OK;
@@ -556,20 +575,7 @@ int Problem::allocate()
         T.Jsuf = u + 1 < d - 1 ? H.kd[u + 1].Jfull : nullptr;
         T.cand = K.cand;
     }
-    // the first sweep searches the initial superblocks (one prefix, one
-    // suffix, every tile stored): its tile counts are fixed by the geometry
-    std::memset(&H.sh0, 0, sizeof H.sh0);
-    for (int u = 0, acc = 0; u < d - 1; ++u) {
-        const KDev &K = H.kd[u];
-        H.sh0.RT[u] = H.sh0.RTs[u] = K.RTn;
-        H.sh0.CT[u] = H.sh0.CTs[u] = K.CTq;
-        H.sh0.soff[u] = acc;
-        const int nst = stored_tiles(K.nk, K.nk1, K.TR);
-        H.sh0.lsp[u] = stored_split(nst, d - 1, K.smax);
-        H.sh0.ntl[u] = nst << H.sh0.lsp[u];
-        acc += H.sh0.ntl[u];
-        H.sh0.soff[u + 1] = acc;
-    }
+    first_shapes(H, 1);
     if ((st = dalloc((void **)&dP, sizeof(ProbDev))) != TT_OK) return st;
     HIPCHK(hipMemcpy(dP, &H, sizeof(ProbDev), hipMemcpyHostToDevice));
     allocated = true;
@@ -715,7 +721,7 @@ template <typename V> int Problem::launch_ahead()
             const int k = u + 1;
             const KDev &K = hP.kd[u];
             int nnew, nst;
-            sweep_units(K, rub, rst, k, nk, nnew, nst);
+            sweep_units(K, rub, rst, k, nk, 1, nnew, nst);
             // the commit's first round of candidates: at most this many
             a.cand[u] = K.cand;
             a.ntl_max[u] = rook ? K.nrb * K.ncb

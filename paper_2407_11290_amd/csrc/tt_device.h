@@ -313,13 +313,14 @@ __host__ __device__ inline int stored_tiles(int rows, int cols, int TR)
 // Parts (2^l) a sweep searches each stored tile of an unfolding in: tall
 // tiles stream best when there are many, but a wavefront takes its tile's
 // rows one batch after another (256 rows about 50 us), so while the tiles of
-// all nk unfoldings would not give every CU sixteen wavefronts they are cut,
-// down to 16 rows (3D n = 32 took 252 us with parts of 32 rows, 248 with 16;
-// parts of 8 made 6D n = 64 379 -> 388 us, more candidates for the commit).
-__host__ __device__ inline int stored_split(int tiles, int nk, int smax)
+// all nk unfoldings of the share problems in the launch would not give every
+// CU sixteen wavefronts they are cut, down to 16 rows (3D n = 32 took 252 us
+// with parts of 32 rows, 248 with 16; parts of 8 made 6D n = 64 379 -> 388 us,
+// more candidates for the commit).
+__host__ __device__ inline int stored_split(int tiles, int nk, int share, int smax)
 {
     int l = 0;
-    while (l < smax && (((int64_t)tiles * nk) << l) < 4096) ++l;
+    while (l < smax && (((int64_t)tiles * nk * share) << l) < 4096) ++l;
     return l;
 }
 

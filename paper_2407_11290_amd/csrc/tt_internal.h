@@ -145,6 +145,9 @@ struct Problem {
     int try_restart(bool &restarted);
 };
 
+// Tile counts of a problem's first sweep, share problems in its launch.
+void first_shapes(ProbDev &H, int share);
+
 // Process-wide table of tuned tile shapes by problem class (tt_tune.hip).
 // Looked up when a problem's tile options are both 0.
 bool tuned_tiles(const Problem &P, int &tr, int &tc);

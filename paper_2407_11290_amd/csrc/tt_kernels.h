@@ -160,12 +160,12 @@ __host__ __device__ inline size_t sweep_lds_bytes(int rk, int TR, int TC, size_t
 
 // Tiles of unfolding k in a sweep whose superblock has ranks up to rub and
 // whose stored region those of rst: new-entry tiles and parts of stored tiles.
-inline void sweep_units(const KDev &K, const int *rub, const int *rst, int k, int nk, int &nnew, int &nst)
+inline void sweep_units(const KDev &K, const int *rub, const int *rst, int k, int nk, int share, int &nnew, int &nst)
 {
     const int all = rub[k - 1] * K.RTn * rub[k + 1] * K.CTq;
     nnew = all - std::min(all, rst[k - 1] * K.RTn * rst[k + 1] * K.CTq);
     nst = stored_tiles(std::min(rub[k - 1], rst[k - 1]) * K.nk, K.nk1 * std::min(rub[k + 1], rst[k + 1]), K.TR);
-    nst <<= stored_split(nst, nk, K.smax);
+    nst <<= stored_split(nst, nk, share, K.smax);
 }
 
 // ---------------------------------------------------------------------------
@@ -1127,7 +1127,7 @@ __device__ inline void scan_cands(gptr_t<const Cand> cand, int i0, int ntl, int 
 // bound on its tile count, so that the first round of candidates is in
 // flight with the state; batches pass PRE = false and a is not read.
 template <typename V, int FNS, bool PRE>
-__device__ void commit_body(const ProbDev *__restrict__ P, ProbState *S, int sweep, int nk, const SweepArgs &a)
+__device__ void commit_body(const ProbDev *__restrict__ P, ProbState *S, int sweep, int nk, int share, const SweepArgs &a)
 {
     // the wavefront index is uniform across the wavefront: saying so keeps the
     // per-unfolding reads scalar
@@ -1384,7 +1384,7 @@ __device__ void commit_body(const ProbDev *__restrict__ P, ProbState *S, int swe
             nn = RT * CT - RTs * CTs;
             // unchanged stored entries are not visited
             ns = s_prop[u] ? stored_tiles(ks[u].nr, ks[u].nc, kTR) : 0;
-            const int lsp = stored_split(ns, nk, s_geo[u][5]);
+            const int lsp = stored_split(ns, nk, share, s_geo[u][5]);
             S->sh.lsp[u] = lsp;
             ns <<= lsp;
             S->sh.ntl[u] = nn + (s_prop[u] ? ns : 1);
@@ -1445,7 +1445,7 @@ __device__ void commit_body(const ProbDev *__restrict__ P, ProbState *S, int swe
 template <typename V, int FNS = 0>
 static __global__ void __launch_bounds__(NTC) k_commit(const ProbDev *__restrict__ P, SweepArgs a)
 {
-    commit_body<V, FNS, true>(P, a.S, a.sweep, a.nk, a);
+    commit_body<V, FNS, true>(P, a.S, a.sweep, a.nk, 1, a);
 }
 
 // ---------------------------------------------------------------------------
@@ -3210,7 +3210,7 @@ static __global__ void __launch_bounds__(NTC) k_commit_b(const ProbDev *__restri
 {
     const ProbDev *P = Pa + bm.p[blockIdx.x];
     const SweepArgs none{};
-    commit_body<V, 0, false>(P, P->S, P->S->sweeps, P->nk, none);
+    commit_body<V, 0, false>(P, P->S, P->S->sweeps, P->nk, bm.na, none);
 }
 
 // Cores of every problem from its final ranks (those of its last commit).

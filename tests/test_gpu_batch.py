@@ -190,3 +190,25 @@ def test_batch_statuses_in_one_call_match_stats():
     sts = batch_run(hs)
     assert sts == [g.stats()["status"] for g in hs]
     assert sts[:4] == [0] * 4 and sts[4:] == [NOT_CONVERGED] * 2
+
+
+@pytest.mark.parametrize("count", [1, 2, 5])
+@pytest.mark.parametrize("n,caps,rows,grid", [
+    ([300, 260, 140], [20, 18], 256, 1),       # parts of 16 rows of tall tiles
+    ([130, 120, 33, 60], [9, 17, 8], 0, 2),    # the default's 64 rows
+])
+def test_few_problems_search_tall_tiles_in_parts(n, caps, rows, grid, count):
+    """Stored tiles of a batch are cut while few problems share its launches:
+    the bits of the single solves."""
+    print("[case]", n, rows, count, flush=True)
+    kw = dict(precision=PREC_FP64, grid=[grid] * len(n), tile_rows=rows, tile_cols=64 if rows else 0)
+    gs, hs = ([TTCross(n, 0.0, FN_HILBERT, seed=i, **kw) for i in range(count)] for _ in range(2))
+    for x in gs + hs:
+        x.set_rank_caps(caps)
+    batch_run(hs)
+    for g, h in zip(gs, hs):
+        g.run()
+        assert list(g.ranks()) == list(h.ranks()) == [1] + caps + [1]
+        for k in range(1, len(n)):
+            assert np.array_equal(g.history(k).view(np.uint64), h.history(k).view(np.uint64)), k
+        assert np.array_equal(g.cores_flat().view(np.uint64), h.cores_flat().view(np.uint64))

@@ -321,3 +321,19 @@ def test_batched_sweeps_have_a_workgroup_per_new_tile(fake, count):
     assert all(g >= {count} * 8 for g in grids[2:6]), grids
     assert all(list(p.ranks()) == [1, 6, 6, 1] for p in ps)
     """)
+
+
+@pytest.mark.parametrize("count,least", [(1, 128), (4, 4 * 128), (64, 64 * 16)])
+def test_stored_tiles_are_cut_while_few_problems_share_a_launch(fake, count, least):
+    """Tiles of 256 rows (16 a superblock of 512 x 512 points): one problem's
+    are searched in parts of 16 rows, and so on until the launch has 4096."""
+    fake(f"""
+    from paper_2407_11290_amd.api import batch_run
+    F.fake_sweeps(2)
+    ps = [TTCross([512] * 3, 1e-8, FN_HILBERT, precision=PREC_FP64, seed=i, r_max=2, tile_rows=256, tile_cols=64)
+          for i in range({count})]
+    F.fake_clear()
+    batch_run(ps)
+    grids = [int(x.split("grid ")[1]) for x in log("k_sweep_b")]
+    assert grids[0] >= {least} and not faults(), (grids, faults())
+    """)
