@@ -3341,6 +3341,7 @@ static __global__ void __launch_bounds__(NT) k_tt_eval(TTArgs a, const double *_
 // every sum keep their order.
 constexpr int TE_LDS_RANK = 8;               // largest rank of this kernel
 constexpr int TE_LDS_MAX = 8192;             // doubles of cores it takes to LDS, at most
+constexpr int TE_LDS_WGS = 1024;             // workgroups, at most
 
 static __global__ void __launch_bounds__(NT) k_tt_eval_lds(TTArgs a, const double *__restrict__ G, int64_t m,
                                                            const int *__restrict__ idx, double *__restrict__ out)
@@ -3387,8 +3388,11 @@ static __global__ void __launch_bounds__(NT) k_tt_eval_lds(TTArgs a, const doubl
 // with one rounding each, so the sums are those of the fma chain, bit for
 // bit.  A fibre is read from L2 once per chunk instead of once per index, the
 // next one while this one is used.  At the other inner modes a lane group
-// reads its own fibre for every index.
+// reads its own fibre for every index (RM = 64 takes no such mode: it took up
+// to 1.6 times what the lane groups of k_tt_eval took).
 constexpr int TE_V = 16384;                  // row-vector entries per workgroup
+__host__ __device__ constexpr int te_chunk(int RM) { return TE_V / RM; }     // indices of a workgroup
+__host__ __device__ constexpr int te_bins(int RM) { return te_chunk(RM) / 4; } // indices of a mode that is sorted, at most
 __host__ __device__ constexpr int te_threads(int RM) { return RM == 16 ? 1024 : 512; }
 
 // Inclusive prefix sum over the wavefront (row shifts, then the row totals
@@ -3475,8 +3479,8 @@ static __global__ void __launch_bounds__(te_threads(RM)) k_tt_eval_sort(TTArgs a
                                                                         int64_t m, const int *__restrict__ idx,
                                                                         double *__restrict__ out)
 {
-    constexpr int TN = te_threads(RM), S = TE_V / RM, PP = S * RM / TN, NW = TN / 64;
-    constexpr int NBIN = S / 4;                  // indices of a mode that is sorted, at most
+    constexpr int TN = te_threads(RM), S = te_chunk(RM), PP = S * RM / TN, NW = TN / 64;
+    constexpr int NBIN = te_bins(RM);
     constexpr int BL = NBIN / 64;                // bins per lane of the scan
     static_assert(S <= TN && RM % 16 == 0 && NBIN % 64 == 0 && S <= 65536, "one index per thread; whole DPP rows");
     __shared__ double V[TE_V];
@@ -3513,7 +3517,7 @@ static __global__ void __launch_bounds__(te_threads(RM)) k_tt_eval_sort(TTArgs a
             const int64_t sa = (int64_t)n * rb;
             const int ik = i;
             i = index(k + 1);                    // the next mode's, in flight meanwhile
-            if (n <= NBIN) {
+            if (RM == 64 || n <= NBIN) {
                 // counting sort: bin sizes (the buffer was cleared during the
                 // last mode's steps), their prefix sums, the order
                 int *const bin = bins[k & 1], *const other = bins[(k & 1) ^ 1];
@@ -3582,7 +3586,7 @@ static __global__ void __launch_bounds__(te_threads(RM)) k_tt_eval_sort(TTArgs a
                         fibre(g, t + NW);
                     }
                 }
-            } else {
+            } else if constexpr (RM < 64) {
                 int *const other = bins[(k & 1) ^ 1];
                 for (int e = tid; e <= NBIN; e += TN) other[e] = 0;
                 if (tid < S) key[tid] = ik;
@@ -3618,15 +3622,60 @@ static __global__ void __launch_bounds__(te_threads(RM)) k_tt_eval_sort(TTArgs a
     }
 }
 
-// Where the kernels cross, by measurement (us a call; host work about 15 of
-// each): the LDS kernel is level with the lane groups at 4000 indices of the
-// 6D Maxwellian (18.4 each), 18.5 against 21.1 at 10007 and 32 against 383 at
-// a million.  The sorting one, ranks 14-16 at n = 64: 54 against 62 at 65536,
-// 179 against 706 at a million; rank 25 at n = 1000 (not sorted): 88 against
-// 84 at 65536, 92 against 153 at 131072, 590 against 1037 at a million.  It
-// takes one chunk of 16384 / RM indices per CU at a time, 40 us each at d = 6:
-// the sorts, the matrix instructions and the fibre reads a quarter each.
-constexpr int64_t TE_LDS_MIN = 4096, TE_SORT_MIN = 65536, TE_SORT_MIN_WIDE = 98304;
+// Which kernel takes m values of a TT: the one with the least of these times
+// (us), fitted to calls of 4096 to a million indices on tensors of 3 to 6
+// modes of 20 to 1000 points at ranks 1 to 64.
+//   lane groups   linear in m: a read of the row vector and a round of eight
+//                 terms per mode;
+//   LDS           the TT's copy into every workgroup, then the sums, in rounds
+//                 of the workgroups a CU holds (two at 64 KB of cores);
+//   sorted        rounds of one chunk per CU, whole rounds: a call of 65536
+//                 indices costs what one of 262144 does at ranks up to 16.  A
+//                 mode with too many indices to sort costs several sorted ones.
+// Against counts and ranks alone (the LDS kernel from 4096 indices, sorted
+// chunks from 65536 and above rank 16 from 98304), us before / now: n = 1000,
+// d = 3, rank 5 at 65536 52 / 30, rank 20 at 132000 149 / 124, rank 40 at
+// 98304 342 / 265; n = 20, d = 6, rank 8 at 4096 29 / 18; n = 30 ... 600, d = 5,
+// rank 5 at 65536 86 / 40.  Where sorting wins it does as before: n = 64, d = 4,
+// rank 20 at 98304 48 against the lane groups' 135.
+enum TEKernel { TE_GROUPS, TE_LDS, TE_SORT };
+constexpr int64_t TE_LDS_MIN = 4096, TE_SORT_MIN = 65536, TE_SORT_MIN_WIDE = 98304;   // fitted from here on
+
+inline TEKernel te_kernel(const TTArgs &a, int64_t m)
+{
+    const int d = a.d;
+    const double len = (double)a.goff[d];
+    int rmax = 1;
+    double rounds = 0, terms = 0;                // of eight terms / multiply-adds per index
+    for (int k = 0; k < d; ++k) {
+        rmax = std::max(rmax, a.ranks[k]);
+        if (k > 0) rounds += (a.ranks[k] + 7) / 8;
+        terms += (double)a.ranks[k] * a.ranks[k + 1];
+    }
+    const int RM = rmax <= 16 ? 16 : rmax <= 32 ? 32 : 64;
+    constexpr int64_t CU = 256;
+    TEKernel best = TE_GROUPS;
+    double t = 17 + 1e-3 * (double)m * (RM == 16 ? 0.074 + 0.052 * rounds : RM == 32 ? 0.106 + 0.1095 * rounds
+                                                                                 : 0.27 + 0.212 * rounds);
+    if (rmax <= TE_LDS_RANK && len <= TE_LDS_MAX && m >= TE_LDS_MIN) {
+        const int64_t wgs = std::min<int64_t>((m + NT - 1) / NT, TE_LDS_WGS), held = CU * std::min<int64_t>(8, 163840 / (int64_t)(8 * len));
+        const double x = 15.5 + (double)((wgs + held - 1) / held) *
+                                    (0.00044 * len + 0.045 * terms * (double)((m + NT * wgs - 1) / (NT * wgs)));
+        if (x < t) { t = x; best = TE_LDS; }
+    }
+    if (m >= (RM == 16 ? TE_SORT_MIN : TE_SORT_MIN_WIDE)) {
+        double c = RM == 16 ? 8 : RM == 32 ? 18 : 41;
+        bool can = true;
+        for (int k = 1; k + 1 < d; ++k) {
+            if (a.n[k] <= te_bins(RM)) c += RM == 16 ? 4.5 + 0.042 * a.n[k] : RM == 32 ? 6 + 0.05 * a.n[k] : 60 + 0.6 * rmax;
+            else if (RM == 64) can = false;
+            else c += RM == 16 ? 29 : 54;
+        }
+        const double x = 16 + c * (double)((m + CU * te_chunk(RM) - 1) / (CU * te_chunk(RM)));
+        if (can && x < t) best = TE_SORT;
+    }
+    return best;
+}
 
 // Launch of the TT's values at m indices.
 inline hipError_t launch_tt_eval(const TTArgs &a, const double *G, int64_t m, const int *idx, double *out,
@@ -3635,19 +3684,24 @@ inline hipError_t launch_tt_eval(const TTArgs &a, const double *G, int64_t m, co
     if (m <= 0) return hipSuccess;
     int rmax = 1;
     for (int k = 1; k < a.d; ++k) rmax = std::max(rmax, a.ranks[k]);
-    const int64_t len = a.goff[a.d];
-    if (rmax <= TE_LDS_RANK && len <= TE_LDS_MAX && m >= TE_LDS_MIN) {
-        const unsigned g = (unsigned)std::min<int64_t>((m + NT - 1) / NT, 1024);
-        k_tt_eval_lds<<<g, NT, sizeof(double) * (size_t)len, stream>>>(a, G, m, idx, out);
-    } else if (m >= (rmax <= 16 ? TE_SORT_MIN : TE_SORT_MIN_WIDE)) {
-        const int S = TE_V / (rmax <= 16 ? 16 : rmax <= 32 ? 32 : 64);
+    switch (te_kernel(a, m)) {
+    case TE_LDS: {
+        const unsigned g = (unsigned)std::min<int64_t>((m + NT - 1) / NT, TE_LDS_WGS);
+        k_tt_eval_lds<<<g, NT, sizeof(double) * (size_t)a.goff[a.d], stream>>>(a, G, m, idx, out);
+        break;
+    }
+    case TE_SORT: {
+        const int RM = rmax <= 16 ? 16 : rmax <= 32 ? 32 : 64, S = te_chunk(RM);
         const unsigned g = (unsigned)std::min<int64_t>((m + S - 1) / S, 1 << 20);
-        if (rmax <= 16) k_tt_eval_sort<16><<<g, te_threads(16), 0, stream>>>(a, G, m, idx, out);
-        else if (rmax <= 32) k_tt_eval_sort<32><<<g, te_threads(32), 0, stream>>>(a, G, m, idx, out);
+        if (RM == 16) k_tt_eval_sort<16><<<g, te_threads(16), 0, stream>>>(a, G, m, idx, out);
+        else if (RM == 32) k_tt_eval_sort<32><<<g, te_threads(32), 0, stream>>>(a, G, m, idx, out);
         else k_tt_eval_sort<64><<<g, te_threads(64), 0, stream>>>(a, G, m, idx, out);
-    } else {
+        break;
+    }
+    default: {
         const int64_t waves = std::min<int64_t>(m, 65536);
         k_tt_eval<<<(unsigned)((waves * 64 + NT - 1) / NT), NT, 0, stream>>>(a, G, m, idx, out);
+    }
     }
     return hipGetLastError();
 }

@@ -1,8 +1,9 @@
 // A host-only stand-in for the HIP runtime calls that libttcross.so makes, to
 // be loaded before the real runtime: device memory is host memory, every
 // launch runs at once on the calling thread.  Kernels do nothing, but
-//   k_commit      ends the run at rank 1 (it writes the host mirror),
-//   k_cores       fills the cores with 1, 2, 3, ... and leaves a clean state,
+//   k_commit      ends the run at rank fake_ranks, as far as the capacities go
+//                 (it writes the host mirror),
+//   k_cores(_t)   fills the cores with 1, 2, 3, ... and leaves a clean state,
 //   k_copy_one    copies and raises its flag,
 //   k_commit_b    lets every problem of the launch grow by one rank a sweep, to
 //                 fake_sweeps sweeps, and k_state_out_b leaves clean states.
@@ -39,7 +40,7 @@ thread_local hipError_t last = hipSuccess;
 void (*hook)(const char *, const void *) = nullptr;
 // a batched launch's problems (as in tt_kernels.h)
 struct Batch { int na; int boff[513]; uint16_t p[512]; };
-int batch_sweeps = 1;
+int batch_sweeps = 1, run_rank = 1;
 struct Config { dim3 g, b; size_t lds; hipStream_t s; };
 thread_local std::vector<Config> configs;
 
@@ -121,7 +122,8 @@ hipError_t launch(const void *fn, dim3 grid, void **args, hipStream_t s)
     if (name.find("k_commit") != std::string::npos && name.find("k_commit_b") == std::string::npos) {
         const ProbDev *P = *(const ProbDev **)args[0];
         HostMirror *hm = P->hm;
-        for (int k = 0; k <= P->d; ++k) hm->r[k] = 1;
+        hm->r[0] = hm->r[P->d] = 1;
+        for (int k = 1; k < P->d; ++k) hm->r[k] = run_rank < P->kd[k - 1].rk_cap ? run_rank : P->kd[k - 1].rk_cap;
         hm->stop = 1;
         hm->sweeps_done = ((const SweepArgs *)args[1])->sweep + 1;
     } else if (name.find("k_commit_b") != std::string::npos) {
@@ -143,14 +145,14 @@ hipError_t launch(const void *fn, dim3 grid, void **args, hipStream_t s)
             memset(hS + bo.p[b], 0, sizeof *hS);
             hS[bo.p[b]].sweeps = batch_sweeps;
         }
-    } else if (name.find("7k_cores") != std::string::npos) {
+    } else if (name.find("7k_cores") != std::string::npos || name.find("k_cores_t") != std::string::npos) {
         const ProbDev *P = *(const ProbDev **)args[0];
         double *G = *(double **)args[2];
         int64_t len = 0;
         for (int j = 0; j < P->d; ++j) len += P->F.n[j];
         if (touch(G, 8 * len, dev, "k_cores"))
             for (int64_t i = 0; i < len; ++i) G[i] = (double)(i + 1);
-        ProbState *hS = *(ProbState **)args[3];
+        ProbState *hS = *(ProbState **)args[name.find("k_cores_t") != std::string::npos ? 4 : 3];
         memset(hS, 0, sizeof *hS);
         hS->sweeps = 1;
     } else if (name.find("k_copy_one") != std::string::npos) {
@@ -188,6 +190,7 @@ extern "C" {
 void fake_hook(void (*f)(const char *, const void *)) { hook = f; }
 void fake_set_device(int d) { cur = d; }
 void fake_sweeps(int n) { batch_sweeps = n; }
+void fake_ranks(int r) { run_rank = r; }
 void fake_limit(size_t bytes) { std::lock_guard<std::recursive_mutex> l(mu); limit = bytes ? in_use + bytes : ~(size_t)0; }
 void fake_fail(const char *name, int nth) { std::lock_guard<std::recursive_mutex> l(mu); fail_at[name] = nth; }
 size_t fake_in_use() { std::lock_guard<std::recursive_mutex> l(mu); return in_use; }

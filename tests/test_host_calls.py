@@ -337,3 +337,43 @@ def test_stored_tiles_are_cut_while_few_problems_share_a_launch(fake, count, lea
     grids = [int(x.split("grid ")[1]) for x in log("k_sweep_b")]
     assert grids[0] >= {least} and not faults(), (grids, faults())
     """)
+
+
+# where the kernels' measured times lie well apart (lane groups / other, us)
+TT_EVAL_KERNELS = [
+    ([1000] * 3, 5, 65536, "9k_tt_evalE"),                 # 30 / 52
+    ([1000] * 3, 5, 262144, "k_tt_eval_sortILi16E"),       # 66 / 53
+    ([1000] * 3, 12, 65536, "9k_tt_evalE"),                # 38 / 52
+    ([1000] * 3, 20, 98304, "k_tt_eval_sortILi32E"),       # 100 / 86
+    ([1000] * 3, 20, 132000, "9k_tt_evalE"),               # 124 / 149
+    ([1000] * 3, 40, 98304, "9k_tt_evalE"),                # 265 / 342
+    ([1000] * 3, 40, 1000000, "9k_tt_evalE"),              # 2430 / 2583
+    ([250] * 4, 24, 132000, "9k_tt_evalE"),                # 167 / 267
+    ([250] * 4, 9, 200000, "k_tt_eval_sortILi16E"),        # 99 / 53
+    ([64] * 4, 9, 65536, "k_tt_eval_sortILi16E"),          # 46 / 35
+    ([64] * 4, 20, 98304, "k_tt_eval_sortILi32E"),         # 135 / 48
+    ([64] * 4, 48, 132000, "9k_tt_evalE"),                 # 560 / 658
+    ([64] * 4, 56, 131072, "k_tt_eval_sortILi64E"),        # 642 / 475
+    ([30, 500, 40, 600, 30], 5, 65536, "9k_tt_evalE"),     # 40 / 86
+    ([20] * 6, 8, 4096, "9k_tt_evalE"),                    # 18 / 29
+    ([20] * 6, 8, 65536, "k_tt_eval_lds"),                 # 44 / 30
+    ([128] * 6, 2, 20000, "k_tt_eval_lds"),
+    ([40, 30, 20], 1, 4097, "k_tt_eval_lds"),
+    ([64] * 6, 16, 1000000, "k_tt_eval_sortILi16E"),       # 623 / 169
+]
+
+
+def test_tt_values_take_the_kernel_that_is_faster(fake):
+    fake(f"""
+    for n, r, m, want in {TT_EVAL_KERNELS!r}:
+        F.fake_ranks(r)
+        p = TTCross(n, 1e-8, FN_HILBERT, precision=PREC_FP64, r_max=64, n_samples=1)
+        p.run()
+        assert max(p.ranks()) == r, p.ranks()
+        idx, out = F.fake_malloc(4 * m * len(n), 0), F.fake_malloc(8 * m, 0)
+        F.fake_clear()
+        assert L.tt_eval(p.h, m, C.c_void_p(idx), C.c_void_p(out), 1) == 0
+        got = [x.split()[1] for x in log("k_tt_eval")]
+        assert len(got) == 1 and want in got[0], (n, r, m, want, got)
+        p.close()
+    """)
