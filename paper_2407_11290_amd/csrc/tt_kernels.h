@@ -3714,39 +3714,32 @@ inline hipError_t launch_tt_eval(const TTArgs &a, const double *G, int64_t m, co
 // start of the round, so the loads of round r+1 are in flight while round r
 // is evaluated.  When the function's per-mode table fits (tab_lds) the
 // workgroup first copies it to LDS, so every table read is an LDS read.
-// VEC (indices 16-byte aligned, as the chunks of ch entries then are): four
-// indices a load.  Bound by HBM: 2^24 FP32 entries of the 6D Maxwellian (470
-// MB) take 101 us, 104 with single loads.
+// Bound by HBM: 2^24 FP32 entries of the 6D Maxwellian (470 MB) take 101 us.
+// A load takes consecutive indices over the threads, so lists of any alignment
+// run alike; 16-byte loads of aligned lists were no faster (104 us), and left
+// four consecutive indices a thread, 109 us and up to a third more, to others.
 constexpr int EV_KP = 16;                   // index ints per thread and round
-// Entries of a round: a multiple of four, so that every chunk starts aligned.
-__host__ __device__ inline int fn_eval_chunk(int d) { return (NT * EV_KP / d) & ~3; }
 constexpr int EV_TAB_LDS_MAX = 32768;       // bytes of table copied to LDS, at most
 
 __host__ __device__ inline size_t fn_eval_idx_bytes() { return (size_t)NT * EV_KP * sizeof(int); }
 
-template <typename V, bool VEC>
+template <typename V>
 static __global__ void __launch_bounds__(NT) k_fn_eval(FnDev F, int64_t m, const int *__restrict__ idx,
                                                        V *__restrict__ out, int tab_lds)
 {
     extern __shared__ __align__(16) unsigned char smem_raw[];
     const int d = F.d, tid = threadIdx.x;
-    const int ch = fn_eval_chunk(d);
+    const int ch = (NT * EV_KP) / d;
     const int64_t stride = (int64_t)gridDim.x * ch;
     int *sidx = (int *)smem_raw;
-    typedef int ivec4 __attribute__((ext_vector_type(4)));
-    ivec4 pf[EV_KP / 4];
+    int pf[EV_KP];
     auto fetch = [&](int64_t b) {
         const int nint = (b < m) ? (int)min((int64_t)ch, m - b) * d : 0;
-        const gptr_t<const int> src = as_global(idx) + (b < m ? b : 0) * d;
+        const int *src = idx + (b < m ? b : 0) * d;
 #pragma unroll
-        for (int r = 0; r < EV_KP / 4; ++r) {
-            const int i = 4 * (tid + r * NT);
-            if (VEC && i + 4 <= nint) {
-                pf[r] = *(gptr_t<const ivec4>)(src + i);
-            } else {
-#pragma unroll
-                for (int j = 0; j < 4; ++j) pf[r][j] = (i + j < nint) ? src[i + j] : 0;
-            }
+        for (int r = 0; r < EV_KP; ++r) {
+            const int i = tid + r * NT;
+            pf[r] = (i < nint) ? src[i] : 0;
         }
     };
     auto rounds = [&](const V *tb) {
@@ -3756,7 +3749,7 @@ static __global__ void __launch_bounds__(NT) k_fn_eval(FnDev F, int64_t m, const
             const int cnt = (int)min((int64_t)ch, m - base);
             __syncthreads();                // the previous round's reads of sidx are done
 #pragma unroll
-            for (int r = 0; r < EV_KP / 4; ++r) *(ivec4 *)(sidx + 4 * (tid + r * NT)) = pf[r];
+            for (int r = 0; r < EV_KP; ++r) sidx[tid + r * NT] = pf[r];
             __syncthreads();
             fetch(base + stride);
             for (int e = tid; e < cnt; e += NT) {
@@ -3787,16 +3780,15 @@ inline hipError_t launch_fn_eval(const FnDev &F, int64_t m, const int *idx, V *o
     const size_t tab_bytes = (size_t)F.tab_rows * F.tab_ld * sizeof(V);
     const int tab_lds = (fn_table<V>(F) && tab_bytes > 0 && tab_bytes <= EV_TAB_LDS_MAX) ? 1 : 0;
     const size_t lds = fn_eval_idx_bytes() + (tab_lds ? tab_bytes : 0);
-    const int ch = fn_eval_chunk(F.d);
+    const int ch = (NT * EV_KP) / F.d;
     const int64_t rounds = (m + ch - 1) / ch;
     const unsigned g = (unsigned)std::min<int64_t>(rounds, 2048);
-    auto kern = ((uintptr_t)idx & 15) == 0 ? k_fn_eval<V, true> : k_fn_eval<V, false>;
     if (ev_start && ev_stop) {
         // the events take the dispatch's own start and end timestamps
-        hipExtLaunchKernelGGL(kern, dim3(g), dim3(NT), (uint32_t)lds, stream, ev_start, ev_stop, 0u, F, m,
+        hipExtLaunchKernelGGL(k_fn_eval<V>, dim3(g), dim3(NT), (uint32_t)lds, stream, ev_start, ev_stop, 0u, F, m,
                               idx, out, tab_lds);
     } else {
-        kern<<<g, NT, lds, stream>>>(F, m, idx, out, tab_lds);
+        k_fn_eval<V><<<g, NT, lds, stream>>>(F, m, idx, out, tab_lds);
     }
     return hipGetLastError();
 }

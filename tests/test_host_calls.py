@@ -377,3 +377,22 @@ def test_tt_values_take_the_kernel_that_is_faster(fake):
         assert len(got) == 1 and want in got[0], (n, r, m, want, got)
         p.close()
     """)
+
+
+def test_bulk_evaluation_has_one_kernel_for_every_alignment(fake):
+    """Index lists that start between 16-byte lines (slices of a larger list)
+    take the kernel that aligned ones take: a second one was slower."""
+    fake("""
+    for f32 in (0, 1):
+        names = set()
+        for d in (2, 3, 5, 6):
+            n = np.array([9] * d, dtype=np.int32)
+            idx, out = F.fake_malloc(4 * 5000 * d + 64, 0), F.fake_malloc(8 * 5000, 0)
+            for shift in (0, 4, 8, 12):
+                F.fake_clear()
+                assert (L.tt_fn_eval_f32 if f32 else L.tt_fn_eval)(
+                    FN_HILBERT, d, n.ctypes.data_as(C.POINTER(C.c_int32)), None, 0, 5000, C.c_void_p(idx + shift),
+                    C.c_void_p(out), 1) == 0
+                names.add(log("k_fn_eval")[0].split()[1])
+        assert len(names) == 1, names
+    """)
