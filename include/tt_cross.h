@@ -108,10 +108,10 @@ typedef struct tt_options {
     int32_t pivot_mode;         /* enum tt_pivot_mode (default greedy) */
     int32_t n_samples;          /* N_s sample entries for rms and the first pivot (default 16384) */
     int32_t grid[TT_MAX_D];     /* subtensor blocks per mode C_j (default 1; 1 <= C_j <= n_j) */
-    int32_t tile_rows;          /* rows per workgroup tile, 1..256; 0 (with tile_cols 0) = the
-                                   tuned shape of the problem's class (tt_autotune), else the
-                                   library's default */
-    int32_t tile_cols;          /* columns per workgroup tile, 1..64 (rounded up to a power of
+    int32_t tile_rows;          /* rows per search tile, 1..256 (see Tile-shape autotuning below);
+                                   0 (with tile_cols 0) = the tuned shape of the problem's class
+                                   (tt_autotune), else the library's default */
+    int32_t tile_cols;          /* columns per new-entry tile, 1..64 (rounded up to a power of
                                    two); 0 as for tile_rows */
     int32_t lookahead;          /* sweeps queued ahead of the host's stop check (default 2;
                                    tt_batch_run queues one round more) */
@@ -251,17 +251,24 @@ int tt_cross_wait(tt_cross_h h);
 /* ranks[0..d] = (1, r_1, .., r_{d-1}, 1) after a run. */
 int tt_cross_get_ranks(tt_cross_h h, int32_t *ranks);
 
-/* Tile shapes of the last run's search launches, one per unfolding:
- * rows[k-1] x cols[k-1] for k = 1..d-1 (see tt_autotune below). */
+/* Tile shapes in force in the last run, one per unfolding: tile_rows in
+ * rows[k-1], tile_cols in cols[k-1] for k = 1..d-1, as requested, tuned or
+ * chosen.  What they mean for the two kinds of search tiles is said under
+ * Tile-shape autotuning below. */
 int tt_cross_get_tiles(tt_cross_h h, int32_t *rows, int32_t *cols);
 
 /* Copy the cores G_1..G_d, concatenated, each r_{k-1} x n_k x r_k in row-major
  * order, into out (cap doubles).  Returns the number of doubles needed; with
- * out == NULL only the size is returned. */
+ * out == NULL only the size is returned.  The copy is complete, and visible to
+ * every stream, when the call returns.  A small copy from a handle with a
+ * stream of its own may run on a stream that such handles share. */
 int64_t tt_cross_get_cores(tt_cross_h h, double *out, int64_t cap, int on_device);
 
 /* Evaluate the TT at m multi-indices idx (m x d, 0-based, row-major) into
- * out[m]; each matrix product is accumulated in ascending index order. */
+ * out[m]; each matrix product is accumulated in ascending index order.
+ * on_device = 0: every index is checked (TT_EINVAL if outside [0, n_j)); = 1:
+ * indices are not checked and must lie in range (one that does not may read
+ * outside the cores). */
 int tt_eval(tt_cross_h h, int64_t m, const int32_t *idx, double *out, int on_device);
 
 /* Pivots of unfolding k (1 <= k <= d-1) in insertion order: rows (r_k x k)
@@ -367,9 +374,12 @@ int tt_batch_statuses(tt_cross_h *hs, int count, int32_t *status);
 /* ---------------------------------------------------------------------------
  * Tile-shape autotuning (batching: tiles chosen by measurement).
  *
- * A search tile covers tile_rows superblock rows by tile_cols columns inside
- * one subtensor block (Sec. 3) and one prefix (suffix) of the nested index
- * sets.  The result of a solve does not depend on the tile shape -- entries
+ * The search has two kinds of tiles.  A tile of new entries covers min(
+ * tile_rows, 128) superblock rows by tile_cols columns inside one subtensor
+ * block (Sec. 3) and one prefix (suffix) of the nested index sets.  A tile of
+ * stored entries covers tile_rows rows by 64 columns wherever blocks,
+ * prefixes and suffixes end, whole or in parts of 16 rows and more; tile_cols
+ * does not enter it.  The result of a solve does not depend on either -- entries
  * are computed one by one in a fixed order, and the tiles' local pivots are
  * combined with the lowest-(row, column) tie-break (Alg. 3) -- only its time
  * does.  The library keeps one process-wide table of tuned shapes by problem
@@ -380,11 +390,12 @@ int tt_batch_statuses(tt_cross_h *hs, int count, int32_t *status);
  *
  * Candidates: the default shape, then every power-of-two tile_rows in
  * [8, 256] and tile_cols in [8, 64] up to the longest run of a mode inside
- * one subtensor block; shapes that do not fit in LDS at the rank cap are
- * skipped.  A candidate replaces the default only if it is at least 2%
- * (batches: 5%) faster.  The tuners allocate (each shape has its own tile tables) and
- * leave the handles' options, precision state and results as a solve with
- * the last candidate left them.
+ * one subtensor block; shapes of which tile_rows x tile_cols does not fit in
+ * LDS at the rank cap are refused, also above 128 rows, and skipped here.  A
+ * candidate replaces the default only if it is at least 2% (batches: 5%)
+ * faster.  The tuners allocate (each shape has its own tile tables) and leave
+ * the handles' options, precision state and results as a solve with the last
+ * candidate left them.
  * ------------------------------------------------------------------------- */
 
 /* Times complete solves of h (reps timed runs after one untimed run, median

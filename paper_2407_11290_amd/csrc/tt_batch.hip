@@ -517,9 +517,9 @@ extern "C" int tt_batch_run(tt_cross_h *hs, int count, void *hip_stream)
         }
     }
     hipStream_t stream = hip_stream ? (hipStream_t)hip_stream : hs[0]->p.stream;
-    // the handles' own streams must not still be working on these buffers
-    // a handle's own stream carries its calls alone, which have ended (waiting
-    // for 512 of them cost up to 5 ms); a caller's stream may carry more
+    // nothing may still be working on these buffers: a handle's own stream
+    // carries its calls alone, and they have ended (waiting for 512 of them
+    // cost up to 5 ms); a caller's stream may carry more
     hipStream_t seen = nullptr;
     for (int i = 0; i < count; ++i) {
         const Problem &Q = hs[i]->p;

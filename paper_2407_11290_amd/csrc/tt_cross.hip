@@ -292,7 +292,7 @@ void Problem::release()
     for (hipEvent_t e : prof_events) (void)hipEventDestroy(e);
     prof_events.clear();
     if (hm) { (void)hipHostFree(hm); hm = nullptr; }
-    if (h_out) { (void)hipHostFree(h_out); h_out = nullptr; hS_pinned = nullptr; h_part = nullptr; }
+    if (h_out) { (void)hipHostFree(h_out); h_out = nullptr; h_state = nullptr; h_part = nullptr; }
     for (hipEvent_t &e : run_ev)
         if (e) { (void)hipEventDestroy(e); e = nullptr; }
     fn.free_device();
@@ -613,16 +613,18 @@ void Problem::resolve_geometry()
 //      opt.lookahead ahead of the host's view of the device's progress (the
 //      commit kernels write it to mapped host memory);
 //   2. once the device reports the stop (or the sweep cap is reached): the
-//      cores (Alg. 4) and a copy of the final state to pinned host memory;
-//   3. the sampled-error check of the precision policy, if this run has one;
-//      an FP32 run that misses eps is escalated to FP64 sweeps (back to 1).
+//      cores (Alg. 4), whose last launch also writes the final state to mapped
+//      host memory, and behind them the sampled-error check of the precision
+//      policy, if this run has one (its sums go to mapped memory too);
+//   3. the check's result, looked at after the state; an FP32 run that misses
+//      eps is escalated to FP64 sweeps (back to 1).
 // advance(wait = false) returns as soon as the next step needs the device to
 // get further than it has.
 // ---------------------------------------------------------------------------
 template <typename V> int Problem::begin_sweeps()
 {
     const int nk = d - 1;
-    // events and the pinned copies are kept with the problem: nothing is
+    // events and the mapped memory are kept with the problem: nothing is
     // created or destroyed per run
     if (!run_ev[0]) HIPCHK(hipEventCreate(&run_ev[0]));
     if (!run_ev[1]) HIPCHK(hipEventCreate(&run_ev[1]));
@@ -633,7 +635,7 @@ template <typename V> int Problem::begin_sweeps()
         void *dev = nullptr;
         HIPCHK(hipHostMalloc(&h_out, off + sizeof(double) * 2 * NBV, hipHostMallocMapped | hipHostMallocCoherent));
         HIPCHK(hipHostGetDevicePointer(&dev, h_out, 0));
-        hS_pinned = (ProbState *)h_out;
+        h_state = (ProbState *)h_out;
         h_part = (double *)((char *)h_out + off);
         d_hS = (ProbState *)dev;
         d_hpart = (double *)((char *)dev + off);
@@ -788,8 +790,8 @@ template <typename V> int Problem::launch_ahead()
 }
 
 // Step 1: follow the device's sweeps and keep the queue filled.  Returns 0
-// while sweeping (wait = false only), 1 once the cores and the final-state
-// copy are queued, or an error.
+// while sweeping (wait = false only), 1 once the cores (and the check) are
+// queued, or an error.
 template <typename V> int Problem::poll_sweeps(bool wait)
 {
     // the mapped counter is read in a tight loop; the stream itself (to see
@@ -834,7 +836,7 @@ template <typename V> int Problem::poll_sweeps(bool wait)
     }
 }
 
-// Step 2: the cores by Alg. 4 in FP64, then the final state's copy.
+// Step 2: the cores by Alg. 4 in FP64 with the final state, then the check.
 template <typename V> int Problem::launch_tail()
 {
     // ranks of the final sweep come from the host mirror; without the stop
@@ -919,7 +921,7 @@ int Problem::poll_tail(bool wait)
     float ms = 0.f;
     HIPCHK(hipEventElapsedTime(&ms, run_ev[0], run_ev[1]));
     time_to_eps = ms * 1e-3 + t_first;
-    const ProbState S = *hS_pinned;
+    const ProbState S = *h_state;
     const int serr = S.err ? S.err : hm->singular ? TT_ESINGULAR : 0;
     if (serr) return set_err(serr, "device reported error %d", serr);
     finalize(S, ranks_now);

@@ -90,7 +90,7 @@ struct Problem {
     hipEvent_t run_ev[3] = {nullptr, nullptr, nullptr};  // start / end of a run's device time;
                                              // end of its check
     void *h_out = nullptr;                   // mapped host memory of the two below
-    ProbState *hS_pinned = nullptr, *d_hS = nullptr;     // mapped host copy of the final state, its device address
+    ProbState *h_state = nullptr, *d_hS = nullptr;     // mapped host copy of the final state, its device address
     double *h_part = nullptr, *d_hpart = nullptr;        // the check's partial sums, the same way
     int i0[TT_MAX_D] = {0};
     // sampled-error check and FP32 -> FP64 escalation

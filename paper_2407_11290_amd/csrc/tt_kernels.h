@@ -142,15 +142,6 @@ template <> __device__ inline float vfma<float>(float a, float b, float c) { ret
 // strictly upper triangular index (zp < z)
 __device__ inline int tri(int zp, int z) { return z * (z - 1) / 2 + zp; }
 
-// Copy of a small struct of 32-bit words read through the global address space.
-template <typename T> __device__ inline void load_words(T &dst, const T *src)
-{
-    static_assert(sizeof(T) % 4 == 0, "word-sized struct");
-    const gptr_t<const int> w = as_global((const int *)src);
-#pragma unroll
-    for (int i = 0; i < (int)(sizeof(T) / 4); ++i) ((int *)&dst)[i] = w[i];
-}
-
 // LDS bytes of a new-entry tile: factors of the tile rows and columns and the
 // two pivot-block triangles.
 __host__ __device__ inline size_t sweep_lds_bytes(int rk, int TR, int TC, size_t w)

@@ -128,3 +128,20 @@ def test_last_handles_come_and_go_in_two_threads():
             p.close()
 
     _in_threads(2, work)
+
+
+def test_threads_check_their_own_handles():
+    """The check's workspace is kept between calls and shared by all handles
+    of one thread after the other, a thread that finds it taken allocates:
+    the same error bits, whichever it gets, small checks and such as are too
+    large to be kept (64 MiB, 2.4 million samples at d = 3)."""
+    ps = [_solved([30 + 7 * i, 25, 20 + i], 2 + i, seed=i) for i in range(4)]
+    sizes = [1, 1000, 70000, 2000000, 2600000, 500]
+    want = [[p.sampled_error(R, 5) for R in sizes] for p in ps]
+    _say("checks in threads")
+
+    def work(i):
+        for _ in range(4):
+            assert [ps[i].sampled_error(R, 5) for R in sizes] == want[i]
+
+    _in_threads(len(ps), work)
